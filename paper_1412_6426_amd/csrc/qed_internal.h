@@ -80,11 +80,13 @@ struct ChildArena {
   long long* slot2;   // same-step, pair records: store slot of the positron
   long long cap;      // records (row length of fe)
   unsigned int* cnt;    // [n_inst][waves]: records per (instance, wavefront); offsets after the scan
-  unsigned int* nrec;   // [waves]: records written by each wavefront
+  unsigned int* nrec;   // [waves]: records written by each wavefront (same-step: their
+                        // prefix after the scan)
   long long* base;      // [n_inst][2]: store counts before the append (photon or e-, e+)
   unsigned int* first;  // [waves]: a wavefront's first pool chunk
   unsigned int* next;   // [nchunks]: the chunk after this one in its wavefront's chain
-  unsigned int* used;   // pool chunks handed out (zeroed before each producing kernel)
+  unsigned int* used;   // pool chunks handed out (zeroed before each producing kernel);
+                        // used[1]: records in all (same-step, set by the scan)
   long long per_wave;   // share of each wavefront (records)
   long long pool0;      // first pool record (waves * per_wave)
   long long nchunks;    // pool chunks
@@ -337,7 +339,8 @@ struct StepArgs {
   int refill_min;  // a lepton wavefront refills idle lanes once this many are idle (or all)
   int adaptive, forced, emission, pairs, push_photons, freeze_on_drop;
   int generations;  // children advanced in their birth step: generations (0: none)
-  long long tile;  // particles per work chunk (0: one chunk per wavefront)
+  long long tile;    // particles per work chunk (0: chosen from the particle count)
+  long long spread;  // wavefronts that few leptons are spread over (one a SIMD)
   WorkHdr* hdr;
   long long* n0;
   long long* lep_pref;

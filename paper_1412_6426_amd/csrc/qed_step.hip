@@ -48,6 +48,24 @@ constexpr int kStageCap = 32;      // staged photon children per wavefront
 // contiguous range per wavefront, which scatters the reads over the whole store).
 constexpr long long kDefaultTile = 128;
 
+// Particles per chunk for N particles on W wavefronts.  Asked for: that.  Else kDefaultTile
+// while every wavefront gets a chunk; below that 64, one batch of lanes each, so that no
+// wavefront takes two batches in turn beside idle ones; and where there are fewer than 64
+// leptons for each of `spread` wavefronts (one a SIMD; 0 for the photons, whose loads want
+// full batches), as few as spread them over all of those.  A lepton's sub-steps are a serial
+// chain, and one of a wavefront with few lanes takes 1.3 us where a full one, with emissions
+// in nearly every sub-step, takes 3.7.  Against 128 throughout: 10^4 electrons in a uniform B
+// 78 to 55 us a step, the lepton kernel of 400 electrons with thousands of sub-steps each 5.7
+// to 3.5 ms.
+__device__ __forceinline__ long long chunk_size(long long N, long long W, long long tile,
+                                                long long spread) {
+  if (tile > 0) return tile;
+  if (N >= kDefaultTile * W) return kDefaultTile;
+  if (spread <= 0 || N >= 64 * spread) return 64;
+  const long long t = (N + spread - 1) / spread;
+  return t < 1 ? 1 : t;
+}
+
 // ------------------------------------------------------------------------------------
 // prep / finalize
 // ------------------------------------------------------------------------------------
@@ -579,14 +597,13 @@ struct TileCursor {
 struct WaveRange {
   long long g, gend, chunk, T, W, N;
 
-  __device__ __forceinline__ void init(long long n, long long tile) {
+  __device__ __forceinline__ void init(long long n, long long tile, long long spread) {
     const long long wpb = blockDim.x >> 6;
     W = (long long)gridDim.x * wpb;
     const long long wv = (long long)blockIdx.x * wpb +
                          __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     N = n;
-    T = tile > 0 ? tile : kDefaultTile;
-    if (T < 1) T = 1;
+    T = chunk_size(N, W, tile, spread);
     chunk = wv - W;
     g = gend = 0;
   }
@@ -621,11 +638,10 @@ struct WaveRange {
 };
 
 // Does this workgroup own any work?  (its first wavefront's first chunk starts below N)
-__device__ __forceinline__ bool block_has_work(long long N, long long tile) {
+__device__ __forceinline__ bool block_has_work(long long N, long long tile, long long spread) {
   const long long wpb = blockDim.x >> 6;
-  long long T = tile > 0 ? tile : kDefaultTile;
-  if (T < 1) T = 1;
-  return (long long)blockIdx.x * wpb * T < N;
+  return (long long)blockIdx.x * wpb *
+             chunk_size(N, (long long)gridDim.x * wpb, tile, spread) < N;
 }
 
 template <bool MIXED>
@@ -825,7 +841,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   const long long N = hdr->lep_total;
   const int wid = wave_index();
   block_stats_init(bs);
-  if (!block_has_work(N, a.tile)) {
+  if (!block_has_work(N, a.tile, a.spread)) {
     if (a.pa.waves > 0 && lane_id() == 0) a.pa.nrec[wid] = 0u;
     __syncthreads();
     block_stats_store(bs, a.lep_part);
@@ -854,7 +870,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   WaveCounters wc;
   TileCursor tc;
   WaveRange wr;
-  wr.init(N, a.tile);
+  wr.init(N, a.tile, a.spread);
   bool open = true;
   int staged = 0;
   // arena: this wavefront's share, then pool chunks
@@ -1320,7 +1336,7 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   block_stats_init(bs);
   stage_bounds<MIXED>(a, sbound);
   __syncthreads();
-  if (!block_has_work(N, a.tile)) {
+  if (!block_has_work(N, a.tile, 0)) {
     if (lane_id() == 0) a.candn[wid] = 0u;
     block_stats_store(bs, a.pho_part);
     return;
@@ -1340,7 +1356,7 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   WaveCounters wc;
   TileCursor tc;
   WaveRange wr;
-  wr.init(N, a.tile);
+  wr.init(N, a.tile, 0);
 
   // Software pipeline: the next 64 photons' columns (in this piece or the next one) are
   // requested before the current ones are processed, so each wavefront keeps a load batch
@@ -1762,43 +1778,68 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 // (in place), the store count before the append into base[], and the counts raised by the
 // totals, clamped to the capacities; the copy kernel drops and counts the children that land
 // beyond them.
-__global__ void __launch_bounds__(1024) arena_scan_kernel(StepArgs a, ChildArena pa,
-                                                          ChildArena qa) {
-  __shared__ unsigned long long wsum[16];
-  const int i = blockIdx.x;
+// Exclusive prefix over n words by a workgroup of 1024: thread t sums the run [t k, t k + k),
+// one scan of the thread sums, then the run's offsets in place.  Returns the total; `wsum` is
+// 16 words of LDS.
+__device__ __forceinline__ unsigned long long block_prefix(unsigned int* row, int n,
+                                                           unsigned long long* wsum) {
   const int lane = lane_id();
   const int wv = (int)(threadIdx.x >> 6);
   const int nw = (int)(blockDim.x >> 6);
+  const int k = (n + (int)blockDim.x - 1) / (int)blockDim.x;
+  const int j0 = (int)threadIdx.x * k;
+  const int j1 = j0 + k < n ? j0 + k : n;
+  unsigned long long v = 0ull;
+  for (int j = j0; j < j1; ++j) v += row[j];
+  unsigned long long x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wv] = x;
+  __syncthreads();
+  unsigned long long run = x - v, carry = 0;
+  for (int q = 0; q < nw; ++q) {
+    if (q < wv) run += wsum[q];
+    carry += wsum[q];
+  }
+  for (int j = j0; j < j1; ++j) {
+    const unsigned c = row[j];
+    row[j] = (unsigned)run;
+    run += c;
+  }
+  __syncthreads();  // wsum is taken again
+  return carry;
+}
+
+// With same-step processing (A.slot set) one more workgroup turns each arena's record counts
+// per producing wavefront into their prefix, and the total goes to used[1], so that the next
+// generation's wavefronts find the records they are dealt.  `in_p`, `in_q`: totals of the
+// records that the producing generation read (null: not one): where both are 0 it made none,
+// and only the totals are set.
+__global__ void __launch_bounds__(1024) arena_scan_kernel(StepArgs a, ChildArena pa,
+                                                          ChildArena qa,
+                                                          const unsigned int* in_p,
+                                                          const unsigned int* in_q) {
+  __shared__ unsigned long long wsum[16];
+  const int i = blockIdx.x;
+  const bool none = in_p && *in_p == 0u && *in_q == 0u;
+  if (i == a.n_inst) {
+    for (int kind = 0; kind < 2; ++kind) {
+      const ChildArena& A = kind == 0 ? pa : qa;
+      if (A.waves <= 0) continue;
+      const unsigned long long total = none ? 0ull : block_prefix(A.nrec, A.waves, wsum);
+      if (threadIdx.x == 0) A.used[1] = (unsigned)total;
+    }
+    return;
+  }
+  if (none) return;
   for (int kind = 0; kind < 2; ++kind) {
     const ChildArena& A = kind == 0 ? pa : qa;
     if (A.waves <= 0) continue;
     unsigned int* row = A.cnt + (size_t)i * A.waves;
-    // thread t takes the run [t k, t k + k) of the row: its sum, one scan of the thread
-    // sums over the workgroup, then the run's offsets
-    const int k = (A.waves + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int j0 = (int)threadIdx.x * k;
-    const int j1 = j0 + k < A.waves ? j0 + k : A.waves;
-    unsigned long long v = 0ull;
-    for (int j = j0; j < j1; ++j) v += row[j];
-    unsigned long long x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[wv] = x;
-    __syncthreads();
-    unsigned long long run = x - v, carry = 0;
-    for (int q = 0; q < nw; ++q) {
-      if (q < wv) run += wsum[q];
-      carry += wsum[q];
-    }
-    for (int j = j0; j < j1; ++j) {
-      const unsigned c = row[j];
-      row[j] = (unsigned)run;
-      run += c;
-    }
-    __syncthreads();  // wsum is taken again for the next arena
+    const unsigned long long carry = block_prefix(row, A.waves, wsum);
     if (threadIdx.x == 0) {
       qed_instance& I = a.inst[i];
       if (kind == 0) {
@@ -1838,6 +1879,13 @@ __device__ __forceinline__ void count_drops(const StepArgs& a, int inst, bool lo
   }
 }
 
+// Records of producing wavefront sw (after the scan).
+__device__ __forceinline__ long long wave_records(const ChildArena& A, int sw) {
+  if (!A.slot) return (long long)A.nrec[sw];
+  const unsigned end = sw + 1 < A.waves ? A.nrec[sw + 1] : A.used[1];
+  return (long long)(end - A.nrec[sw]);
+}
+
 // One wavefront per producing wavefront: walks its records in order and gives each the
 // next store slot of its instance after the offsets of the scan (a per-instance running
 // count in LDS), then writes the child (photon) or both children (pair record), and, for
@@ -1875,15 +1923,15 @@ __global__ void __launch_bounds__(256) arena_copy_kernel(StepArgs a, ChildArena 
   const uint64_t below = lanes_below();
   const int lane = lane_id();
   const uint32_t step = (uint32_t)a.hdr->step;
-  const int npa = pa.waves;
-  const int nqa = qa.waves;
+  const int npa = pa.waves > 0 && !(pa.slot && pa.used[1] == 0u) ? pa.waves : 0;
+  const int nqa = qa.waves > 0 && !(qa.slot && qa.used[1] == 0u) ? qa.waves : 0;
   const int V = nblk * (int)(blockDim.x >> 6);
   const int wid = blk * (int)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   for (int t = wid; t < npa + nqa; t += V) {
     const bool pair = t >= npa;
     const ChildArena& A = pair ? qa : pa;
     const int sw = pair ? t - npa : t;
-    const long long n = (long long)A.nrec[sw];
+    const long long n = wave_records(A, sw);
     if (n == 0) continue;
     for (int q = lane; q < a.n_inst; q += 64) run[q] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -2037,47 +2085,54 @@ struct GenWave {
   ArenaTally tp, tq;
 };
 
-// A wavefront's stream of children: the records of producing wavefronts wid, wid + V, ...
-// of arena A, one item per photon record or two (electron, positron) per pair record,
-// handed out in pieces of consecutive items of one producing wavefront.
+// A wavefront's stream of children: all records of arena A in the order of their producing
+// wavefronts are one index space, one item per photon record or two (electron, positron) per
+// pair record, dealt in chunks over the V wavefronts.  The children of one parent, or of one
+// busy wavefront, thus spread over the whole GPU: a generation lasts as long as the longest
+// chain of sub-steps, where wavefronts that took over the records of one producer each ran
+// through hundreds of chains while the others were idle (the large-step shower of 125 seeds,
+// three steps: 47.9 to 19.5 ms).
 struct GenStream {
-  int t = 0, V = 1;
-  long long j = 0, n = 0;  // next item, items of producing wavefront t
-  bool pair = false, open = false;
-  ArenaWalk walk;
+  long long n = 0, j = 0, jend = 0, next_chunk = 0, V = 1;
+  int c = 1;  // items of a chunk
+  bool pair = false;
   __device__ __forceinline__ void init(const ChildArena& A, int wid, int v, bool is_pair) {
-    t = wid;
     V = v;
     pair = is_pair;
-    open = A.waves > 0 && t < A.waves;
-    n = open ? (pair ? 2 : 1) * (long long)A.nrec[t] : 0;
-    j = 0;
+    n = A.waves > 0 ? (pair ? 2 : 1) * (long long)A.used[1] : 0;
+    const long long per = n / (4 * V);
+    c = per < 1 ? 1 : per > 64 ? 64 : (int)per;
+    next_chunk = wid;
   }
   // The next piece [j0, j0 + take), take <= want <= 64; false once the stream is exhausted.
   // Wavefront-uniform; all lanes call.
-  __device__ __forceinline__ bool next(const ChildArena& A, int want, long long& j0, int& take) {
-    while (open && j >= n) {
-      t += V;
-      if (t >= A.waves) {
-        open = false;
-        break;
-      }
-      n = (pair ? 2 : 1) * (long long)A.nrec[t];
-      j = 0;
-      walk = ArenaWalk{};
+  __device__ __forceinline__ bool next(int want, long long& j0, int& take) {
+    if (j >= jend) {
+      j = next_chunk * c;
+      if (j >= n) return false;
+      jend = j + c < n ? j + c : n;
+      next_chunk += V;
     }
-    if (!open) return false;
-    take = (int)((long long)want < n - j ? (long long)want : n - j);
+    take = (int)((long long)want < jend - j ? (long long)want : jend - j);
     j0 = j;
-    const long long rec0 = pair ? (j0 >> 1) : j0;
-    const long long rec1 = pair ? ((j0 + take + 1) >> 1) : j0 + take;
-    walk.advance(A, t, rec0, rec1 - rec0, pair ? (n >> 1) : n);
     j += take;
     return true;
   }
-  // Record holding item jj of the current piece.
+  // Record holding item jj.
   __device__ __forceinline__ long long record(const ChildArena& A, long long jj) const {
-    return walk.index(A, t, pair ? (jj >> 1) : jj);
+    const unsigned i = (unsigned)(pair ? jj >> 1 : jj);
+    int lo = 0, hi = A.waves;  // nrec[lo] <= i < nrec[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (A.nrec[mid] <= i) lo = mid;
+      else hi = mid;
+    }
+    long long k = (long long)(i - A.nrec[lo]);
+    if (k < A.per_wave) return (long long)lo * A.per_wave + k;
+    k -= A.per_wave;
+    unsigned chunk = A.first[lo];
+    for (; k >= kArenaChunk; k -= kArenaChunk) chunk = A.next[chunk];
+    return A.pool0 + (long long)chunk * kArenaChunk + k;
   }
 };
 
@@ -2109,7 +2164,7 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
     while (freem) {
       long long j0;
       int take;
-      if (!st.next(A, __popcll(freem), j0, take)) break;
+      if (!st.next(__popcll(freem), j0, take)) break;
       const int rank = __popcll(freem & below);
       bool act = false;
       if (slot < 0 && rank < take) {
@@ -2292,7 +2347,8 @@ __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArg
   const qed_soa& S = a.sp[QED_PHOTON];
   const bool photons = a.push_photons || a.pairs;
   GenStream st;
-  st.init(A, gw.wid, V, false);
+  // from the last wavefront on, so that few photons and few leptons meet on none
+  st.init(A, V - 1 - gw.wid, V, false);
   long long slot = -1;
   int inst = 0, nsub = 0, k = 0;
   uint64_t id = 0, seed = 0;
@@ -2304,7 +2360,7 @@ __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArg
     while (freem) {
       long long j0;
       int take;
-      if (!st.next(A, __popcll(freem), j0, take)) break;
+      if (!st.next(__popcll(freem), j0, take)) break;
       const int rank = __popcll(freem & below);
       bool act = false;
       if (slot < 0 && rank < take) {
@@ -2450,11 +2506,39 @@ __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArg
   }
 }
 
+// Is any wavefront of this workgroup dealt one of n items (of the lepton or the photon stream)?
+__device__ __forceinline__ bool gen_block_has_work(long long n, bool leptons) {
+  const long long wpb = blockDim.x >> 6, V = (long long)gridDim.x * wpb;
+  const long long per = n / (4 * V);
+  const long long c = per < 1 ? 1 : per > 64 ? 64 : per;
+  const long long first = leptons ? (long long)blockIdx.x * wpb
+                                  : V - ((long long)blockIdx.x + 1) * wpb;
+  return first * c < n;
+}
+
 template <bool MIXED, int FMODE, bool RUNS>
 __device__ __forceinline__ void gen_pass(const StepArgs& a, const GenArgs& q) {
   using Tab = typename TabType<MIXED>::T;
   __shared__ BlockStats bs;
   __shared__ Tab tab[kTableN];  // the emission table, as in the lepton kernel
+  // a workgroup without a child writes its empty counts (only the first pass stores its
+  // statistics; the scan takes a generation without children at all as empty)
+  const unsigned np = q.ipa.waves > 0 ? q.ipa.used[1] : 0u;
+  const unsigned nq = q.iqa.waves > 0 ? q.iqa.used[1] : 0u;
+  if (np == 0u && nq == 0u) {
+    if (q.pass > 1) return;
+  }
+  const bool work = gen_block_has_work(np, false) || gen_block_has_work(2ll * nq, true);
+  if (!work) {
+    if (lane_id() == 0) {
+      if (q.opa.waves > 0) q.opa.nrec[wave_index()] = 0u;
+      if (q.oqa.waves > 0) q.oqa.nrec[wave_index()] = 0u;
+    }
+    if (q.pass == 1)
+      for (int i = threadIdx.x; i < kPfCount; i += blockDim.x)
+        a.gen_part[(size_t)i * kMaxGridBlocks + blockIdx.x] = 0ull;
+    return;
+  }
   block_stats_init(bs);
   {
     const Tab* src = MIXED ? reinterpret_cast<const Tab*>(a.tables->ab32)
@@ -2535,7 +2619,9 @@ static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape ph
   const bool gen = a.generations > 0;
   const int rb = gen ? 0 : kReduceBlocks;
   if (src > 0) {
-    hipLaunchKernelGGL(arena_scan_kernel, dim3(a.n_inst), dim3(1024), 0, s, a, a.pa, a.qa);
+    const unsigned int* no = nullptr;
+    hipLaunchKernelGGL(arena_scan_kernel, dim3(a.n_inst + (gen ? 1 : 0)), dim3(1024), 0, s, a,
+                       a.pa, a.qa, no, no);
     // with same-step processing the copy also clears generation 1's count matrices
     hipLaunchKernelGGL(arena_copy_kernel,
                        dim3(rb + (src + kWavesPerBlock - 1) / kWavesPerBlock), dim3(256), 0, s,
@@ -2557,7 +2643,11 @@ static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape ph
       hipLaunchKernelGGL((gen_kernel<MIXED, FMODE>), dim3(a.gen_grid), dim3(256), 0, s, a, q);
     const int gsrc = q.opa.waves + q.oqa.waves;
     const bool more = g < a.generations;
-    hipLaunchKernelGGL(arena_scan_kernel, dim3(a.n_inst), dim3(1024), 0, s, a, q.opa, q.oqa);
+    // (both input arenas are on, or the photon one alone: its total then serves twice)
+    const unsigned int* in_p = q.ipa.used + 1;
+    const unsigned int* in_q = q.iqa.waves > 0 ? q.iqa.used + 1 : in_p;
+    hipLaunchKernelGGL(arena_scan_kernel, dim3(a.n_inst + 1), dim3(1024), 0, s, a, q.opa, q.oqa,
+                       in_p, in_q);
     hipLaunchKernelGGL(arena_copy_kernel, dim3((gsrc + kWavesPerBlock - 1) / kWavesPerBlock),
                        dim3(256), 0, s, a, q.opa, q.oqa, more ? a.gpa[(g + 1) % 2] : none,
                        more ? a.gqa[(g + 1) % 2] : none, 0);
