@@ -8,12 +8,14 @@
 #include <stdint.h>
 
 #include "qed.h"
+#include "qed_math.h"
 
 namespace qedk {
 
 constexpr double kAlpha = 7.2973525693e-3;  // fine-structure constant, CODATA 2018
 constexpr double kPi = 3.141592653589793238;
 constexpr double kInvSqrt3Pi = 0.18377629847393068;  // 1 / (sqrt(3) pi)
+constexpr double kLog10Of2 = 0.30102999566398120;
 constexpr int kTableN = QED_TABLE_N;
 constexpr double kLog2ZLo = -20.0;  // first node z = 2^-20
 constexpr double kLog2ZHi = 7.0;    // last node z = 2^7; functions vanish beyond
@@ -137,52 +139,58 @@ struct Series64 {
   double b0, b1, c0, c1, c2;
 };
 
-__device__ __forceinline__ void series_bc(const Series64& s, double z, double& b, double& c) {
-  const double z23 = cbrt(z * z);
+// The two tabulated functions at kZLo <= z < kZHi, times e^z and combined as x + cB y.
+__device__ __forceinline__ double2 table_at(const double2* tab, const MathTab& mt, double z) {
+  const double u = (log2_normal(mt, z) - kLog2ZLo) * kNodesPerLog2;
+  const int i = min((int)u, kTableN - 2);
+  const double f = u - (double)i;
+  const double2 g0 = tab[i];
+  const double2 g1 = tab[i + 1];
+  return make_double2(g0.x + f * (g1.x - g0.x), g0.y + f * (g1.y - g0.y));
+}
+
+// z^(2/3) of the small-z series (below the normal range, the library's cube root).
+__device__ __forceinline__ double series_z23(const MathTab& mt, double z) {
+  return z >= kFastLo ? pow23_normal(mt, z) : cbrt(z * z);
+}
+__device__ __forceinline__ void series_bc(const MathTab& mt, const Series64& s, double z,
+                                          double& b, double& c) {
+  const double z23 = series_z23(mt, z);
   const double z43 = z23 * z23;
   b = s.b0 / z23 + s.b1 * z23 + 0.75 * s.b0 * z43;
   c = s.c0 - s.c1 * z23 - s.c2 * z43;
 }
 
-// A(z) + cB * B(z)
-__device__ __forceinline__ double emission_bracket64(const double2* tab, const Series64& s,
-                                                     double z, double cB) {
-  if (z >= kZLo && z < kZHi) {
-    const double u = (log2(z) - kLog2ZLo) * kNodesPerLog2;
-    const int i = min((int)u, kTableN - 2);
-    const double f = u - (double)i;
-    const double2 g0 = tab[i];
-    const double2 g1 = tab[i + 1];
-    const double ga = g0.x + f * (g1.x - g0.x);
-    const double gb = g0.y + f * (g1.y - g0.y);
-    return (ga + cB * gb) * exp(-z);
+// A(z) + cB * B(z).  The tabulated range runs without a branch (on a clamped z); below it
+// the series, above it 0.  NaN propagates.
+__device__ __forceinline__ double emission_bracket64(const double2* tab, const MathTab& mt,
+                                                     const Series64& s, double z, double cB) {
+  const double zc = fmin(fmax(z, kZLo), kZHi);
+  const double2 g = table_at(tab, mt, zc);
+  double v = (g.x + cB * g.y) * exp_neg(mt, zc);
+  v = z >= kZHi ? 0.0 : v;
+  if (!(z >= kZLo)) {
+    v = z == 0.0 ? __builtin_inf() : z;
+    if (z > 0.0) {
+      double b, c;
+      series_bc(mt, s, z, b, c);
+      v = (2.0 * b - c) + cB * b;
+    }
   }
-  if (z >= kZHi) return 0.0;
-  if (z > 0.0) {
-    double b, c;
-    series_bc(s, z, b, c);
-    return (2.0 * b - c) + cB * b;
-  }
-  return z == 0.0 ? __builtin_inf() : z;  // NaN propagates
+  return v;
 }
 
 // cB * B(z) + C(z)
-__device__ __forceinline__ double pair_bracket64(const double2* tab, const Series64& s, double z,
-                                                 double cB) {
+__device__ __forceinline__ double pair_bracket64(const double2* tab, const MathTab& mt,
+                                                 const Series64& s, double z, double cB) {
   if (z >= kZLo && z < kZHi) {
-    const double u = (log2(z) - kLog2ZLo) * kNodesPerLog2;
-    const int i = min((int)u, kTableN - 2);
-    const double f = u - (double)i;
-    const double2 g0 = tab[i];
-    const double2 g1 = tab[i + 1];
-    const double gb = g0.x + f * (g1.x - g0.x);
-    const double gc = g0.y + f * (g1.y - g0.y);
-    return (cB * gb + gc) * exp(-z);
+    const double2 g = table_at(tab, mt, z);
+    return (cB * g.x + g.y) * exp_neg(mt, z);
   }
   if (z >= kZHi) return 0.0;
   if (z > 0.0) {
     double b, c;
-    series_bc(s, z, b, c);
+    series_bc(mt, s, z, b, c);
     return cB * b + c;
   }
   return z == 0.0 ? __builtin_inf() : z;
@@ -245,42 +253,124 @@ struct V3 {
   double x, y, z;
 };
 
+// The roundings of the state's update are written out (fma or not), so that a particle's
+// trajectory does not depend on what the compiler contracts around it: in a standing wave a
+// last-place difference grows by many orders of magnitude within a few periods.
 __device__ __forceinline__ V3 cross(const V3& a, const V3& b) {
-  return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
+  return {fma(a.y, b.z, -(a.z * b.y)), fma(a.z, b.x, -(a.x * b.z)), fma(a.x, b.y, -(a.y * b.x))};
 }
 __device__ __forceinline__ double dot(const V3& a, const V3& b) {
-  return a.x * b.x + a.y * b.y + a.z * b.z;
+  return fma(a.z, b.z, fma(a.x, b.x, a.y * b.y));
 }
+__device__ __forceinline__ V3 scale(double f, const V3& a) { return {f * a.x, f * a.y, f * a.z}; }
+// a + f b, one rounding each
+__device__ __forceinline__ V3 axpy(double f, const V3& b, const V3& a) {
+  return {fma(f, b.x, a.x), fma(f, b.y, a.y), fma(f, b.z, a.z)};
+}
+__device__ __forceinline__ V3 add(const V3& a, const V3& b) {
+  return {a.x + b.x, a.y + b.y, a.z + b.z};
+}
+// a - f a, one rounding each (the momentum a photon has taken)
+__device__ __forceinline__ V3 recoil(const V3& a, double f) { return axpy(-f, a, a); }
 
-// chi = eps_r sqrt((gamma E + p x B)^2 - (p.E)^2), Eq. (4); for photons gamma -> |k|.
-__device__ __forceinline__ double chi_of(const V3& p, double energy, const V3& E, const V3& B,
-                                         double eps_r) {
-  const V3 pb = cross(p, B);
-  const V3 v = {energy * E.x + pb.x, energy * E.y + pb.y, energy * E.z + pb.z};
+// (chi / eps_r)^2 = (gamma E + p x B)^2 - (p.E)^2, Eq. (4), at least 0 (0 for a NaN); for
+// photons gamma -> |k|.  HAS_B false: B = 0.
+template <bool HAS_B>
+__device__ __forceinline__ double chi_sq(const V3& p, double energy, const V3& E, const V3& B) {
+  const V3 v = HAS_B ? axpy(energy, E, cross(p, B)) : scale(energy, E);
   const double pe = dot(p, E);
-  const double r = dot(v, v) - pe * pe;
-  return eps_r * sqrt(r > 0.0 ? r : 0.0);
+  const double r = fma(-pe, pe, dot(v, v));
+  return r > 0.0 ? r : 0.0;
 }
 
-// Boris push (Appendix A): half E kick, B rotation, half E kick; charge q = +-1.
-__device__ __forceinline__ void boris(V3& p, double qh2, const V3& E, const V3& B) {
-  // qh2 = q h / 2
-  V3 pm = {p.x + qh2 * E.x, p.y + qh2 * E.y, p.z + qh2 * E.z};
-  const double ig = qh2 / sqrt(1.0 + dot(pm, pm));
-  const V3 t = {ig * B.x, ig * B.y, ig * B.z};
-  const double sfac = 2.0 / (1.0 + dot(t, t));
-  const V3 c1 = cross(pm, t);
-  const V3 pp = {pm.x + c1.x, pm.y + c1.y, pm.z + c1.z};
-  const V3 s = {sfac * t.x, sfac * t.y, sfac * t.z};
-  const V3 c2 = cross(pp, s);
-  p = {pm.x + c2.x + qh2 * E.x, pm.y + c2.y + qh2 * E.y, pm.z + c2.z + qh2 * E.z};
+// A square root with what its divisions need: the correctly rounded root of x >= 0 and, in
+// the fast range, its inverse to a unit in the last place.
+struct Root {
+  double r, inv;
+  bool fast;
+  // a / r, correctly rounded
+  __device__ __forceinline__ double under(double a) const {
+    return fast ? div_normal(a, r, inv) : a / r;
+  }
+};
+__device__ __forceinline__ Root root_of(double x) {
+  Root o;
+  o.fast = x >= kFastLo && x <= kFastHi;
+  if (o.fast) {
+    o.inv = rsqrt_normal(x);
+    o.r = sqrt_from_rsqrt(x, o.inv);
+  } else {
+    o.r = sqrt(x);
+    o.inv = 0.0;
+  }
+  return o;
+}
+
+// A lepton's momentum in its fields: p^2, gamma with its inverse, (chi / eps_r)^2.
+struct Kin {
+  double p2, c2;
+  Root g;
+};
+template <bool HAS_B>
+__device__ __forceinline__ Kin kin_of(const V3& p, const V3& E, const V3& B) {
+  Kin k;
+  k.p2 = dot(p, p);
+  k.g = root_of(1.0 + k.p2);
+  k.c2 = chi_sq<HAS_B>(p, k.g.r, E, B);
+  return k;
+}
+
+// The push of one sub-step, with q h / 2 = qh2: Boris (Appendix A: half E kick, B rotation,
+// half E kick), or p + q h E where B = 0 (the rotation is the identity).
+// push_fast runs without a branch, so that the draw's integer rounds fill its latencies; false
+// where an operand leaves the fast range (a momentum beyond 1e135, an infinity or a NaN), and
+// push_any serves those.
+template <bool HAS_B>
+__device__ __forceinline__ bool push_fast(const V3& p0, double qh2, const V3& E, const V3& B,
+                                          V3& p, Kin& k) {
+  bool ok = true;
+  if (HAS_B) {
+    const V3 pm = axpy(qh2, E, p0);
+    const double s0 = 1.0 + dot(pm, pm);
+    const double y0 = rsqrt_normal(s0);
+    const V3 t = scale(div_normal(qh2, sqrt_from_rsqrt(s0, y0), y0), B);
+    const double t2 = 1.0 + dot(t, t);
+    const V3 s = scale(div_normal(2.0, t2, rcp_normal(t2)), t);
+    const V3 pp = add(pm, cross(pm, t));
+    p = axpy(qh2, E, add(pm, cross(pp, s)));
+    ok = s0 <= kFastHi && t2 <= kFastHi;
+  } else {
+    p = axpy(2.0 * qh2, E, p0);
+  }
+  k.p2 = dot(p, p);
+  const double s1 = 1.0 + k.p2;
+  k.g.inv = rsqrt_normal(s1);
+  k.g.r = sqrt_from_rsqrt(s1, k.g.inv);
+  k.g.fast = true;
+  k.c2 = chi_sq<HAS_B>(p, k.g.r, E, B);
+  return ok && s1 <= kFastHi && k.c2 <= kFastHi;
+}
+template <bool HAS_B>
+__device__ __forceinline__ void push_any(const V3& p0, double qh2, const V3& E, const V3& B,
+                                         V3& p, Kin& k) {
+  if (HAS_B) {
+    const V3 pm = axpy(qh2, E, p0);
+    const V3 t = scale(root_of(1.0 + dot(pm, pm)).under(qh2), B);
+    const V3 s = scale(2.0 / (1.0 + dot(t, t)), t);
+    const V3 pp = add(pm, cross(pm, t));
+    p = axpy(qh2, E, add(pm, cross(pp, s)));
+  } else {
+    p = axpy(2.0 * qh2, E, p0);
+  }
+  k = kin_of<HAS_B>(p, E, B);
 }
 
 // dt / dt_q for leptons: dt_q = kappa 14 (2 pi eps_r) (gamma/chi)^(2/3) (Eq. (29), Eq. (6)).
-__device__ __forceinline__ double substep_ratio_lepton(double dt, double chi, double gamma,
-                                                       double inv_lep_scale) {
-  const double r = chi / gamma;
-  return dt * cbrt(r * r) * inv_lep_scale;  // inv_lep_scale = 1/(kappa 28 pi eps_r)
+__device__ __forceinline__ double substep_ratio_lepton(const MathTab& mt, double dt, const Kin& k,
+                                                       double eps_r, double inv_lep_scale) {
+  const double r = k.g.under(eps_r * root_of(k.c2).r);  // chi / gamma
+  const double r23 = (r >= kFastLo && r <= kFastHi) ? pow23_normal(mt, r) : cbrt(r * r);
+  return dt * r23 * inv_lep_scale;  // inv_lep_scale = 1/(kappa 28 pi eps_r)
 }
 // (h / (kappa 28 pi eps_r))^3: a sub-step of length h satisfies Eq. (29) in a state of
 // (chi, gamma) iff this times chi^2 is at most gamma^2 (no cube root on the sub-step path).
@@ -460,9 +550,14 @@ __device__ __forceinline__ uint64_t lanes_below() {
 }
 __device__ __forceinline__ uint64_t wave_ballot(bool b) { return __ballot(b); }
 
-template <typename T>
-__device__ __forceinline__ T wave_bcast(T v, int src) {
-  return __shfl(v, src, 64);
+// Lane src's value in every lane (src wavefront-uniform): v_readlane, no trip through LDS.
+__device__ __forceinline__ int wave_bcast(int v, int src) {
+  return __builtin_amdgcn_readlane(v, src);
+}
+__device__ __forceinline__ long long wave_bcast(long long v, int src) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(unsigned long long)v, src);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)v >> 32), src);
+  return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
 __device__ __forceinline__ void atomic_max_nonneg(double* addr, double v) {

@@ -36,31 +36,34 @@ struct TrialArgs {
   double u0;  // log2 z at delta_min: the first interval's start
   double k0;  // table node index of the first interval's end
   double glx[kGl / 2], glw[kGl / 2];  // positive nodes on [-1, 1] and their weights
+  double z_per_q;  // z = z_per_q delta / (1 - delta): 2 / (3 chi)
+  double pref;     // dtfac / (sqrt(3) pi gamma)
 };
 
 // Eq. (24)'s density P(delta) from the FP64 tables (global memory; L2-resident).
-__device__ __forceinline__ double density(const TrialArgs& a, const Series64& ser, double d) {
+__device__ __forceinline__ double density(const TrialArgs& a, const MathTab& mt,
+                                          const Series64& ser, double d) {
   if (!(d > 0.0 && d < 1.0)) return 0.0;
-  const double omd = 1.0 - d;
-  const double z = (2.0 / 3.0) * d / (omd * a.chi);
-  return (a.dtfac * kInvSqrt3Pi / a.gamma) *
-         emission_bracket64(a.tables->ab64, ser, z, d * d / omd);
+  const double iomd = rcp_normal(1.0 - d);
+  const double z = a.z_per_q * (d * iomd);
+  return a.pref * emission_bracket64(a.tables->ab64, mt, ser, z, d * d * iomd);
 }
 
 // W's integrand in u.
-__device__ __forceinline__ double integrand(const TrialArgs& a, const Series64& ser, double u) {
+__device__ __forceinline__ double integrand(const TrialArgs& a, const MathTab& mt, const Series64& ser,
+                                            double u) {
   const double q = 1.5 * a.chi * exp2(u);
   const double d = q / (1.0 + q);
-  return density(a, ser, d) * 0.6931471805599453 * d / (1.0 + q);
+  return density(a, mt, ser, d) * 0.6931471805599453 * d / (1.0 + q);
 }
 
-__device__ __forceinline__ double gauss_legendre(const TrialArgs& a, const Series64& ser,
-                                                 double lo, double hi) {
+__device__ __forceinline__ double gauss_legendre(const TrialArgs& a, const MathTab& mt,
+                                                 const Series64& ser, double lo, double hi) {
   const double c = 0.5 * (lo + hi), h = 0.5 * (hi - lo);
   double s = 0.0;
 #pragma unroll
   for (int m = 0; m < kGl / 2; ++m)
-    s += a.glw[m] * (integrand(a, ser, c - h * a.glx[m]) + integrand(a, ser, c + h * a.glx[m]));
+    s += a.glw[m] * (integrand(a, mt, ser, c - h * a.glx[m]) + integrand(a, mt, ser, c + h * a.glx[m]));
   return h * s;
 }
 
@@ -76,10 +79,13 @@ __device__ __forceinline__ Series64 series_of(const DevTables* t) {
 }
 
 __global__ void __launch_bounds__(256) w_panel_kernel(TrialArgs a) {
+  __shared__ MathTab mt;
+  stage_math(mt);
+  __syncthreads();
   const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= a.panels) return;
   const Series64 ser = series_of(a.tables);
-  a.part[k] = gauss_legendre(a, ser, edge(a, k), edge(a, k + 1));
+  a.part[k] = gauss_legendre(a, mt, ser, edge(a, k), edge(a, k + 1));
 }
 
 // cum[0] = 0, cum[k + 1] = cum[k] + part[k]: each thread sums one contiguous run, the run
@@ -114,7 +120,8 @@ __global__ void __launch_bounds__(kScanThreads) w_scan_kernel(TrialArgs a) {
 
 // Eq. (22): the root of W(delta) = target, W(1) >= target >= 0 (cum: W at the interval
 // ends, in LDS or global memory).
-__device__ double standard_delta(const TrialArgs& a, const Series64& ser, const double* cum,
+__device__ double standard_delta(const TrialArgs& a, const MathTab& mt, const Series64& ser,
+                                 const double* cum,
                                  double target) {
   long long lo = 0, hi = a.panels;
   while (hi - lo > 1) {
@@ -129,9 +136,9 @@ __device__ double standard_delta(const TrialArgs& a, const Series64& ser, const 
   if (!(u > blo && u < bhi)) u = 0.5 * (blo + bhi);
   const double tol = 0x1p-50 * fmax(fmax(fabs(ua), fabs(ub)), 1.0);
   for (int it = 0; it < 60; ++it) {
-    const double g = gauss_legendre(a, ser, ua, u) - want;
+    const double g = gauss_legendre(a, mt, ser, ua, u) - want;
     if (g > 0.0) bhi = u; else blo = u;
-    const double f = integrand(a, ser, u);
+    const double f = integrand(a, mt, ser, u);
     if (f > 0.0) {
       // converged once the Newton step is below the tolerance (it may then round to u, which
       // is why this is tested before the bracket)
@@ -154,6 +161,9 @@ __device__ double standard_delta(const TrialArgs& a, const Series64& ser, const 
 // The modified and alternative generators (one kernel each, so that both stay lean).
 template <int GEN>
 __global__ void __launch_bounds__(256) trial_kernel(TrialArgs a) {
+  __shared__ MathTab mt;
+  stage_math(mt);
+  __syncthreads();
   const bool ok = a.tables->magic == kTableMagic;
   const Series64 ser = series_of(a.tables);
   const long long stride = (long long)gridDim.x * blockDim.x;
@@ -169,9 +179,9 @@ __global__ void __launch_bounds__(256) trial_kernel(TrialArgs a) {
     double delta = 0.0;
     if (GEN == QED_GEN_MODIFIED) {
       const double d = r1 * r1 * r1;
-      if (r2 < 3.0 * r1 * r1 * density(a, ser, d)) delta = d;
+      if (r2 < 3.0 * r1 * r1 * density(a, mt, ser, d)) delta = d;
     } else {
-      if (r2 < density(a, ser, r1)) delta = r1;
+      if (r2 < density(a, mt, ser, r1)) delta = r1;
     }
     a.out[i] = delta;
   }
@@ -190,6 +200,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 constexpr int kLdsCumMax = 6144;  // 48 KB
 __global__ void __launch_bounds__(256) standard_kernel(TrialArgs a) {
   extern __shared__ double s_cum[];
+  __shared__ MathTab mt;
+  stage_math(mt);
   __shared__ long long s_qi[4][128];
   __shared__ double s_qt[4][128];
   const bool ok = a.tables->magic == kTableMagic;
@@ -237,11 +249,11 @@ __global__ void __launch_bounds__(256) standard_kernel(TrialArgs a) {
       const long long qi_l = qi[qn + lane];
       const double qt_l = qt[qn + lane];
       wave_lds_sync();
-      a.out[qi_l] = standard_delta(a, ser, cum, qt_l);
+      a.out[qi_l] = standard_delta(a, mt, ser, cum, qt_l);
     }
   }
   wave_lds_sync();
-  if (lane < qn) a.out[qi[lane]] = standard_delta(a, ser, cum, qt[lane]);
+  if (lane < qn) a.out[qi[lane]] = standard_delta(a, mt, ser, cum, qt[lane]);
 }
 
 // W(1) gamma / dtfac for chi_i (one workgroup per chi): each thread integrates every 256th
@@ -267,6 +279,9 @@ __device__ __forceinline__ long long panels_for(double chi, double delta_min, do
 
 __global__ void __launch_bounds__(256) w_table_kernel(WTableArgs w) {
   __shared__ double part[256];
+  __shared__ MathTab mt;
+  stage_math(mt);
+  __syncthreads();
   const int i = blockIdx.x;
   const double chi =
       w.n > 1 ? w.chi_min * exp2(w.log2_ratio * (double)i / (double)(w.n - 1)) : w.chi_min;
@@ -275,6 +290,8 @@ __global__ void __launch_bounds__(256) w_table_kernel(WTableArgs w) {
   a.chi = chi;
   a.gamma = 1.0;
   a.dtfac = 1.0;
+  a.z_per_q = (2.0 / 3.0) / chi;
+  a.pref = kInvSqrt3Pi;
   a.panels = panels_for(chi, w.delta_min, a.u0, a.k0);
   for (int m = 0; m < kGl / 2; ++m) {
     a.glx[m] = w.glx[m];
@@ -285,7 +302,7 @@ __global__ void __launch_bounds__(256) w_table_kernel(WTableArgs w) {
   double s = 0.0;
   if (ok)
     for (long long k = threadIdx.x; k < a.panels; k += blockDim.x)
-      s += gauss_legendre(a, ser, edge(a, k), edge(a, k + 1));
+      s += gauss_legendre(a, mt, ser, edge(a, k), edge(a, k + 1));
   part[threadIdx.x] = s;
   __syncthreads();
   for (int h = 128; h > 0; h >>= 1) {
@@ -372,6 +389,8 @@ hipError_t launch_generator_trials(const DevTables* tables, int generator, doubl
   a.chi = chi;
   a.gamma = gamma;
   a.dtfac = dtfac;
+  a.z_per_q = (2.0 / 3.0) / chi;
+  a.pref = dtfac * kInvSqrt3Pi / gamma;
   a.key0 = (uint32_t)key;
   a.key1 = (uint32_t)(key >> 32);
   a.first = first;

@@ -287,14 +287,21 @@ struct LaneCounters {
 
   // One decision r2 < P.  `fold`: P counts for the largest probability of the step (every
   // emission decision; only the pair decisions that make a pair, which include every P >= 1).
+  // One test covers what is rare: P >= 1, a P that is no number, and a near tie.
   __device__ __forceinline__ void note(double P, double r2, bool fold = true) {
-    if (!isfinite(P)) {
-      block_count(*bs, kPfNonfinite);
-      return;
+    const bool plain = P < 1.0;
+    if (fold) maxp = plain ? fmax(maxp, P) : maxp;
+    if (!plain || fabs(r2 - P) < kNearThreshold) {
+      if (!isfinite(P)) {
+        block_count(*bs, kPfNonfinite);
+        return;
+      }
+      if (!plain) {
+        if (fold) maxp = fmax(maxp, P);
+        block_count(*bs, kPfSaturated);
+      }
+      if (fabs(r2 - P) < kNearThreshold) block_count(*bs, kPfNear);
     }
-    if (fold) maxp = fmax(maxp, P);
-    if (P >= 1.0) block_count(*bs, kPfSaturated);
-    if (fabs(r2 - P) < kNearThreshold) block_count(*bs, kPfNear);
   }
 };
 
@@ -328,15 +335,16 @@ __device__ __forceinline__ void block_count(BlockStats& bs, int field) {
 
 // Sub-step refinement (Sec. IV.H asks every sub-interval to satisfy Eq. (29)): a sub-step of
 // length h that ends in the state (chi, gamma^2 = 1 + p2) is taken again at half the length
-// if h > dt_q there, i.e. if hs3 chi^2 > gamma^2 with hs3 = (h / (kappa 28 pi eps_r))^3 --
-// unless that would make more than QED_NSUB_MAX sub-steps (then it is kept and counted as
-// clamped).  h / dt_q within 1e-12 of 1 is counted with the near-integer sub-step ratios.
-__device__ __forceinline__ bool refine_substep(double hs3, double chi, double p2, double g,
-                                               double h, double inv_lep_scale, int k, int left,
-                                               BlockStats& bs) {
-  const double lhs = hs3 * (chi * chi), rhs = 1.0 + p2;
+// if h > dt_q there, i.e. if hs3 (chi / eps_r)^2 > gamma^2 with
+// hs3 = eps_r^2 (h / (kappa 28 pi eps_r))^3 -- unless that would make more than QED_NSUB_MAX
+// sub-steps (then it is kept and counted as clamped).  h / dt_q within 1e-12 of 1 is counted
+// with the near-integer sub-step ratios.
+__device__ __forceinline__ bool refine_substep(const MathTab& mt, double hs3, const Kin& kn,
+                                               double h, double eps_r, double inv_lep_scale,
+                                               int k, int left, BlockStats& bs) {
+  const double lhs = hs3 * kn.c2, rhs = 1.0 + kn.p2;
   if (fabs(lhs - rhs) <= 4e-12 * rhs &&
-      fabs(substep_ratio_lepton(h, chi, g, inv_lep_scale) - 1.0) <= 1e-12)
+      fabs(substep_ratio_lepton(mt, h, kn, eps_r, inv_lep_scale) - 1.0) <= 1e-12)
     block_count(bs, kPfNearInt);
   if (!(lhs > rhs)) return false;
   if (k + 2 * left > QED_NSUB_MAX) {
@@ -653,52 +661,128 @@ struct TabType<true> {
   using T = float2;
 };
 
-// Emission decision of the modified generator (Sec. IV.G, Eqs. (24), (25)) for draw o:
-// delta = r1^3, emit iff r2 < 3 r1^2 P(r1^3).  The mixed form evaluates the rate and the
-// comparison in FP32.
+// One draw of the modified generator (Sec. IV.G): r1, r2, delta = r1^3 and 1 / (1 - delta).
+struct EmissionDraw {
+  double r1, r2, d, iomd;  // FP64 form
+  float f1, f2, fd;        // mixed form
+};
+template <bool MIXED>
+__device__ __forceinline__ EmissionDraw emission_draw(const uint4& o) {
+  EmissionDraw e{};
+  if (MIXED) {
+    e.f1 = uniform32(o.y);
+    e.f2 = uniform32(o.w);
+    e.fd = e.f1 * e.f1 * e.f1;
+  } else {
+    e.r1 = uniform64(o.x, o.y);
+    e.r2 = uniform64(o.z, o.w);
+    e.d = e.r1 * e.r1 * e.r1;
+    e.iomd = rcp_normal(1.0 - e.d);  // 1 - delta >= 2^-52
+  }
+  return e;
+}
+
+// Emission decision (Eqs. (24), (25)): emit iff r2 < 3 r1^2 P(r1^3).  The mixed form evaluates
+// the rate and the comparison in FP32.  One reciprocal of 1 - delta and one of chi (from its
+// square) serve z = (2/3) delta / ((1 - delta) chi) and delta^2 / (1 - delta), and 1 / gamma
+// comes with the state: 0.75 of the time of six divisions and roots.
 template <bool MIXED>
 __device__ __forceinline__ bool emission_decision(const typename TabType<MIXED>::T* tab,
-                                                  const Series64& ser64, const Series32& ser32,
-                                                  const uint4& o, double chi, double g,
+                                                  const MathTab& mt, const Series64& ser64,
+                                                  const Series32& ser32, const EmissionDraw& e,
+                                                  const Kin& kn, double eps_r, double inv_eps_r,
                                                   double dtfac, LaneCounters& cnt,
                                                   double& delta) {
+  // chi = 0 is taken as 2^-450 eps_r: z is beyond the tabulated range and P = 0 either way
+  const double c2 = fmax(kn.c2, kFastLo);
+  const double rc = rsqrt_normal(c2);
+  const bool fast = kn.g.fast && c2 <= kFastHi;
   if (MIXED) {
-    const float r1 = uniform32(o.y), r2 = uniform32(o.w);
-    const float d = r1 * r1 * r1, omd = 1.0f - d;
-    const float z = (2.0f / 3.0f) * d / (omd * (float)chi);
-    const float P = 3.0f * r1 * r1 * ((float)(dtfac * kInvSqrt3Pi) / (float)g) *
+    const float chi = (float)(eps_r * (fast ? sqrt_from_rsqrt(c2, rc) : sqrt(kn.c2)));
+    const float r1 = e.f1, r2 = e.f2;
+    const float d = e.fd, omd = 1.0f - d;
+    const float z = (2.0f / 3.0f) * d / (omd * chi);
+    const float P = 3.0f * r1 * r1 * ((float)(dtfac * kInvSqrt3Pi) / (float)kn.g.r) *
                     emission_bracket32(reinterpret_cast<const float2*>(tab), ser32, z,
                                        d * d / omd);
     cnt.note((double)P, (double)r2);
     delta = (double)d;
     return r2 < P;
   }
-  const double r1 = uniform64(o.x, o.y), r2 = uniform64(o.z, o.w);
-  const double d = r1 * r1 * r1, omd = 1.0 - d;
-  const double z = (2.0 / 3.0) * d / (omd * chi);
-  const double P = 3.0 * r1 * r1 * (dtfac * kInvSqrt3Pi / g) *
-                   emission_bracket64(reinterpret_cast<const double2*>(tab), ser64, z,
-                                      d * d / omd);
-  cnt.note(P, r2);
+  const double d = e.d;
+  double z = (2.0 / 3.0) * (d * e.iomd) * inv_eps_r * rc;
+  double pg = dtfac * kInvSqrt3Pi * kn.g.inv;
+  if (!fast) {
+    z = (2.0 / 3.0) * (d * e.iomd) / (eps_r * sqrt(kn.c2));
+    pg = kn.g.under(dtfac * kInvSqrt3Pi);
+  }
+  const double P = 3.0 * e.r1 * e.r1 * pg *
+                   emission_bracket64(reinterpret_cast<const double2*>(tab), mt, ser64, z,
+                                      d * d * e.iomd);
+  cnt.note(P, e.r2);
   delta = d;
-  return r2 < P;
+  return e.r2 < P;
+}
+
+// One lane's lepton between its sub-steps: sub-step k, `left` sub-steps of length h to go (the
+// current one included).
+struct LepLane {
+  V3 x{}, p{}, E{}, B{};
+  double qh2 = 0.0, h = 0.0, dtfac = 0.0, hs3 = 0.0;
+  int k = 0, left = 0;
+};
+
+// One sub-step of an active lane: the push, the position and the emission decision for the
+// draw o (Sec. IV.G).  A sub-step whose end state breaks Eq. (29) is taken again from its
+// start at half the length (rare: such lanes repeat the push while the others wait).
+template <bool MIXED, bool HAS_B>
+__device__ __forceinline__ bool lepton_substep(const StepArgs& a,
+                                               const typename TabType<MIXED>::T* tab,
+                                               const MathTab& mt, const Series64& ser64,
+                                               const Series32& ser32, uint64_t id, uint64_t seed,
+                                               uint32_t step, bool refine, LepLane& L, Kin& kn,
+                                               BlockStats& bs, LaneCounters& cnt,
+                                               double& delta) {
+  const V3 p0 = L.p;
+  const bool fast = push_fast<HAS_B>(p0, L.qh2, L.E, L.B, L.p, kn);
+  const EmissionDraw e =
+      emission_draw<MIXED>(draw_words(id, seed, step, (uint32_t)L.k, kDraw));
+  // lhs > rhs: refine; within 4e-12 of each other: the ratio may count as near an integer
+  const double rhs = 1.0 + kn.p2;
+  if (!fast || (refine && kn.c2 > 0.0 && fma(L.hs3, kn.c2, -rhs) >= -5e-12 * rhs)) {
+    if (!fast) push_any<HAS_B>(p0, L.qh2, L.E, L.B, L.p, kn);
+    while (refine && kn.c2 > 0.0 &&
+           refine_substep(mt, L.hs3, kn, L.h, a.eps_r, a.inv_lep_scale, L.k, L.left, bs)) {
+      L.h *= 0.5;
+      L.qh2 *= 0.5;
+      L.dtfac *= 0.5;
+      L.hs3 *= 0.125;
+      L.left *= 2;
+      push_any<HAS_B>(p0, L.qh2, L.E, L.B, L.p, kn);
+    }
+  }
+  L.x = axpy(kn.g.under(L.h), L.p, L.x);
+  if (!a.emission) return false;
+  return emission_decision<MIXED>(tab, mt, ser64, ser32, e, kn, a.eps_r, a.inv_eps_r, L.dtfac,
+                                  cnt, delta);
 }
 
 // The photon of an emission: energy delta gamma m c^2 along p (Sec. IV.F), as the factor
 // f = |k| / |p|.  Counts the event's spectrum bin and radiated energy; false (and a
 // non-finite count) if p = 0.
-__device__ __forceinline__ bool emission_photon(const V3& p, double g, double delta, double wgt,
-                                                BlockStats& bs, LaneCounters& cnt, double& f) {
-  const double pabs = sqrt(dot(p, p));
-  if (!(pabs > 0.0)) {
+__device__ __forceinline__ bool emission_photon(const MathTab& mt, const Kin& kn, double delta,
+                                                double wgt, BlockStats& bs, LaneCounters& cnt,
+                                                double& f) {
+  if (!(kn.p2 > 0.0)) {
     block_count(bs, kPfNonfinite);
     return false;
   }
-  const double eps = delta * g;
-  f = eps / pabs;
+  const double eps = delta * kn.g.r;
+  f = root_of(kn.p2).under(eps);
   // bin floor(10 (log10 eps + 8)), in FP64 in both precisions (an emission is rare next to
   // the sub-steps, and the bins then agree with an FP64 count of the same photons)
-  const double lb = floor(10.0 * (log10(eps) + 8.0));
+  const double l2 = (eps >= kFastLo && eps <= kFastHi) ? log2_normal(mt, eps) : log2(eps);
+  const double lb = floor(fma(l2, 10.0 * kLog10Of2, 80.0));
   if (lb >= 0.0 && lb < (double)QED_SPECTRUM_BINS) atomicAdd(&bs.w[kPfHist + (int)lb], 1ull);
   cnt.energy += wgt * eps;
   return true;
@@ -826,7 +910,7 @@ __device__ __forceinline__ void flush_pairs(const StepArgs& a, PairStage& sg, in
 template <bool MIXED, int FMODE, bool EXT>
 struct LeptonShape {
   static constexpr bool global_table = !MIXED && FMODE == kFieldE && !EXT;
-  static constexpr int min_waves = global_table ? 3 : 1;
+  static constexpr int min_waves = global_table || (MIXED && FMODE != kFieldLocal && !EXT) ? 3 : 1;
 };
 
 // RUNS: the reverse mode of Sec. VI (runs_photon > 1) is compiled in (with EXT).
@@ -836,7 +920,9 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   constexpr bool kGlobalTab = LeptonShape<MIXED, FMODE, EXT>::global_table;
   __shared__ Tab tab_lds[kGlobalTab ? 1 : kTableN];
   __shared__ BlockStats bs;
+  __shared__ MathTab mt;
   __shared__ PhotonStage stage[kWavesPerBlock];
+  const MathRow mrow = load_math();
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->lep_total;
   const int wid = wave_index();
@@ -852,6 +938,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   if (!kGlobalTab)
     for (int i = threadIdx.x; i < kTableN; i += blockDim.x) tab_lds[i] = src[i];
   const Tab* tab = kGlobalTab ? src : tab_lds;
+  store_math(mt, mrow);
   __syncthreads();
 
   const Series64 ser64 = {a.tables->series[0], a.tables->series[1], a.tables->series[2],
@@ -878,14 +965,16 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   ArenaCursor acur;
   ArenaTally tally;
 
-  // lane state: sub-step k of the particle in `slot`, `left` sub-steps of length h to go
-  // (the current one included)
+  // lane state: the particle in `slot`
   long long slot = -1;
-  int inst = 0, sp = 0, k = 0, left = 0;
-  V3 x{}, p{}, E{}, B{};
+  int inst = 0, sp = 0;
+  LepLane L;
+  V3 &x = L.x, &p = L.p, &E = L.E, &B = L.B;
+  int &k = L.k, &left = L.left;
+  double &h = L.h;
   uint64_t id = 0, seed = 0;
   uint32_t nev = 0;
-  double qh2 = 0.0, h = 0.0, dtfac = 0.0, wgt = 0.0, hs3 = 0.0;
+  double wgt = 0.0;
   const bool refine = a.forced <= 0 && a.adaptive;
 
   while (true) {
@@ -920,24 +1009,24 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
           if (FMODE == kFieldEB) B = {eb[3], eb[4], eb[5]};
         }
         // chi and the number of sub-steps, once per step from the step-start state
-        const double g = sqrt(1.0 + dot(p, p));
-        const double chi = chi_of(p, g, E, FMODE == kFieldE ? V3{0.0, 0.0, 0.0} : B, a.eps_r);
+        const Kin kn = kin_of<FMODE != kFieldE>(p, E, B);
         // (FP64 in both precisions: n_sub is no part of the FP32 rate evaluation)
         int nsub = 1;
         if (a.forced > 0) {
           nsub = a.forced;
-        } else if (a.adaptive && chi > 0.0) {
-          const NsubInfo ni = nsub_from_ratio(substep_ratio_lepton(a.dt, chi, g, a.inv_lep_scale));
+        } else if (a.adaptive && kn.c2 > 0.0) {
+          const NsubInfo ni =
+              nsub_from_ratio(substep_ratio_lepton(mt, a.dt, kn, a.eps_r, a.inv_lep_scale));
           nsub = ni.n;
           if (ni.near_int) block_count(bs, kPfNearInt);
           if (ni.clamped) block_count(bs, kPfClamped);
         }
-        if (!isfinite(chi)) block_count(bs, kPfNonfinite);
+        if (!isfinite(kn.c2)) block_count(bs, kPfNonfinite);
         atomicAdd(&bs.w[kPfNsub + (nsub < QED_NSUB_HIST ? nsub : QED_NSUB_HIST - 1)], 1ull);
-        h = a.dt / (double)nsub;
-        dtfac = h * a.dtfac_per_h;
-        qh2 = (sp == QED_ELECTRON ? -0.5 : 0.5) * h;
-        hs3 = substep_cube(h, a.inv_lep_scale);
+        h = div_normal(a.dt, (double)nsub, rcp_normal((double)nsub));
+        L.dtfac = h * a.dtfac_per_h;
+        L.qh2 = (sp == QED_ELECTRON ? -0.5 : 0.5) * h;
+        L.hs3 = a.eps_r * a.eps_r * substep_cube(h, a.inv_lep_scale);
         k = 0;
         left = nsub;
       }
@@ -952,45 +1041,18 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
     wc.low_occ += (__popcll(act) < 32);
 
     // ---- one sub-step: push, chi, emission decision (Sec. IV.G) ----
-    // A sub-step whose end state breaks Eq. (29) is taken again from its start at half the
-    // length (rare: such lanes repeat the push while the others wait).
     bool emit = false;
-    double f = 0.0, g = 1.0, chi = 0.0;
+    double f = 0.0;
+    Kin kn{0.0, 0.0, {1.0, 1.0, true}};
     // the weight of an event's photon before any factor: w, or w / N_g in the reverse mode
     // of Sec. VI, whose runs beyond the first follow the first below
     const double wrun = RUNS ? wgt / (double)a.runs_photon : wgt;
     if (slot >= 0) {
-      const V3 p0 = p;
-      for (;;) {
-        if (FMODE == kFieldE) {
-          // B = 0: the Boris rotation is the identity and the push is p += q h E
-          p = {p0.x + 2.0 * qh2 * E.x, p0.y + 2.0 * qh2 * E.y, p0.z + 2.0 * qh2 * E.z};
-        } else {
-          p = p0;
-          boris(p, qh2, E, B);
-        }
-        const double p2 = dot(p, p);
-        g = sqrt(1.0 + p2);
-        chi = chi_of(p, g, E, FMODE == kFieldE ? V3{0.0, 0.0, 0.0} : B, a.eps_r);
-        if (!(refine && chi > 0.0) ||
-            !refine_substep(hs3, chi, p2, g, h, a.inv_lep_scale, k, left, bs))
-          break;
-        h *= 0.5;
-        qh2 *= 0.5;
-        dtfac *= 0.5;
-        hs3 *= 0.125;
-        left *= 2;
-      }
-      const double hg = h / g;
-      x = {x.x + hg * p.x, x.y + hg * p.y, x.z + hg * p.z};
-      if (a.emission) {
-        const uint4 o = draw_words(id, seed, step, (uint32_t)k, kDraw);
-        double delta;
-        emit = emission_decision<MIXED>(tab, ser64, ser32, o, chi, g, dtfac, cnt, delta);
-        if (emit) {
-          emit = emission_photon(p, g, delta, wrun, bs, cnt, f);
-          if (emit) ++nev;
-        }
+      double delta;
+      if (lepton_substep<MIXED, FMODE != kFieldE>(a, tab, mt, ser64, ser32, id, seed, step,
+                                                  refine, L, kn, bs, cnt, delta)) {
+        emit = emission_photon(mt, kn, delta, wrun, bs, cnt, f);
+        if (emit) ++nev;
       }
     }
 
@@ -1084,9 +1146,10 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
         if (slot >= 0 && a.emission) {
           const uint4 o = draw_words(id, seed, step, sc, kDraw);
           double delta;
-          e2 = emission_decision<MIXED>(tab, ser64, ser32, o, chi, g, dtfac, cnt, delta);
+          e2 = emission_decision<MIXED>(tab, mt, ser64, ser32, emission_draw<MIXED>(o), kn,
+                                        a.eps_r, a.inv_eps_r, L.dtfac, cnt, delta);
           if (e2) {
-            e2 = emission_photon(p, g, delta, wrun, bs, cnt, f2);
+            e2 = emission_photon(mt, kn, delta, wrun, bs, cnt, f2);
             if (e2) ++nev;
           }
         }
@@ -1142,8 +1205,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
     }
     if (emit) {
       // recoil: the lepton keeps p - k (momentum conservation, Sec. IV.F)
-      const V3 kq = {f * p.x, f * p.y, f * p.z};
-      p = {p.x - kq.x, p.y - kq.y, p.z - kq.z};
+      p = recoil(p, f);
     }
 
     // ---- lanes whose particle has done all its sub-steps write back and go idle ----
@@ -1209,14 +1271,13 @@ struct PhotonSetup {
 
 // chi_gamma, n_sub and the rate prefactors of one photon in the fields E, B (identical in
 // both photon kernels).  `bound` holds the per-octave pair-rate bounds (staged in LDS).
-template <bool MIXED>
+template <bool MIXED, bool HAS_B>
 __device__ __forceinline__ PhotonSetup photon_setup(const StepArgs& a, const V3& E, const V3& B,
-                                                    const V3& kv, double kabs,
+                                                    const V3& kv, double kabs, double inv_k,
                                                     const double* bound, BlockStats* bs) {
   PhotonSetup ps;
-  const double inv_k = 1.0 / kabs;
   // chi_gamma (Eqs. (31), (32))
-  ps.chi = chi_of(kv, kabs, E, B, a.eps_r);
+  ps.chi = a.eps_r * root_of(chi_sq<HAS_B>(kv, kabs, E, B)).r;
   ps.nsub = 1;
   if (a.forced > 0) {
     ps.nsub = a.forced;
@@ -1230,7 +1291,7 @@ __device__ __forceinline__ PhotonSetup photon_setup(const StepArgs& a, const V3&
     }
   }
   if (bs && !isfinite(ps.chi)) block_count(*bs, kPfNonfinite);
-  const double h = ps.nsub == 1 ? a.dt : a.dt / (double)ps.nsub;
+  const double h = ps.nsub == 1 ? a.dt : div_normal(a.dt, (double)ps.nsub, rcp_normal((double)ps.nsub));
   ps.h = h;
   ps.hk = h * inv_k;
   ps.pref = h * (a.dtfac_per_h * kInvSqrt3Pi) * inv_k;
@@ -1283,8 +1344,8 @@ __device__ __forceinline__ bool below_bound(const uint4& o, double pbound) {
 
 // Exact pair decision of Eq. (30) for draw o; returns r1 through *r1out.
 template <bool MIXED>
-__device__ __forceinline__ bool pair_decision(const StepArgs& a, const Series64& s64,
-                                              const Series32& s32, const uint4& o, double chi,
+__device__ __forceinline__ bool pair_decision(const StepArgs& a, const MathTab& mt,
+                                              const Series64& s64, const Series32& s32, const uint4& o, double chi,
                                               double pref, LaneCounters& cnt, double* r1out) {
   if (MIXED) {
     const float r1 = uniform32(o.y), r2 = uniform32(o.w);
@@ -1296,9 +1357,10 @@ __device__ __forceinline__ bool pair_decision(const StepArgs& a, const Series64&
     return r2 < P;
   }
   const double r1 = uniform64(o.x, o.y), r2 = uniform64(o.z, o.w);
-  const double omd = 1.0 - r1;
-  const double z = (2.0 / 3.0) / (chi * r1 * omd);
-  const double P = pref * pair_bracket64(a.tables->bc64, s64, z, r1 / omd + omd / r1);
+  const double omd = 1.0 - r1;  // r1 and 1 - r1 >= 2^-53
+  const double iv = rcp_normal(r1 * omd);
+  const double z = (2.0 / 3.0) * iv / chi;
+  const double P = pref * pair_bracket64(a.tables->bc64, mt, s64, z, (r1 * r1 + omd * omd) * iv);
   cnt.note(P, r2, r2 < P);
   *r1out = r1;
   return r2 < P;
@@ -1394,14 +1456,16 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
       const uint64_t id = in.id;
       V3 x = in.x;
       const V3 kv = in.k;
-      const double kabs = sqrt(dot(kv, kv));
+      const Root kr = root_of(dot(kv, kv));
+      const double kabs = kr.r, inv_k = kr.under(1.0);
       const bool live = id != QED_ID_DEAD;
       const bool ok = live && kabs > 0.0 && isfinite(kabs);
       if (live && !ok) block_count(bs, kPfNonfinite);
       wc.adv0 += __popcll(wave_ballot(ok));
       if (ok) {
         if (FMODE == kFieldLocal) field_at_position<true>(fld, a.inst[inst].amp, x, E, B);
-        const PhotonSetup st = photon_setup<MIXED>(a, E, B, kv, kabs, sbound, &bs);
+        const PhotonSetup st = photon_setup<MIXED, FMODE != kFieldE>(a, E, B, kv, kabs, inv_k,
+                                                                     sbound, &bs);
         int k = 0;
         for (; k < st.nsub; ++k) {
           if (a.push_photons) x = {x.x + st.hk * kv.x, x.y + st.hk * kv.y, x.z + st.hk * kv.z};
@@ -1449,7 +1513,7 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
         } else {
           unsigned long long pos = 0;
           if (lane == 0) pos = atomicAdd(&hdr->n_cand, (unsigned long long)nc);
-          pos = wave_bcast(pos, 0) + (unsigned long long)__popcll(cm & below);
+          pos = (unsigned long long)wave_bcast((long long)pos, 0) + (unsigned long long)__popcll(cm & below);
           // the overflow list holds one entry per photon slot: never full
           if (cand && pos < (unsigned long long)a.cand_cap) a.cand[pos] = e;
         }
@@ -1475,6 +1539,7 @@ struct ExactCtx {
   ArenaCursor acur;  // this wavefront's place in the pair arena
   ArenaTally tally;
   const double* bound;  // per-octave pair-rate bounds (LDS)
+  const MathTab* mt;    // (LDS)
 };
 
 // The pair records of the lanes with `make` into the wavefront's arena share or pool chunks,
@@ -1566,11 +1631,12 @@ __device__ __forceinline__ ExactCand load_candidate(const StepArgs& a, const Exa
   q.id = S.id[q.s];
   q.x = {S.x[q.s], S.y[q.s], S.z[q.s]};
   q.kv = {S.px[q.s], S.py[q.s], S.pz[q.s]};
-  const double kabs = sqrt(dot(q.kv, q.kv));
+  const Root kr = root_of(dot(q.kv, q.kv));
+  const double kabs = kr.r, inv_k = kr.under(1.0);
   q.seed = a.inst[q.inst].seed;
   if (FMODE == kFieldLocal) field_at_position<true>(c.fld, a.inst[q.inst].amp, q.x, q.E, q.B);
   else instance_fields<FMODE>(a, q.inst, q.E, q.B);
-  q.st = photon_setup<MIXED>(a, q.E, q.B, q.kv, kabs, c.bound, nullptr);
+  q.st = photon_setup<MIXED, FMODE != kFieldE>(a, q.E, q.B, q.kv, kabs, inv_k, c.bound, nullptr);
   return q;
 }
 
@@ -1604,7 +1670,7 @@ __device__ __forceinline__ void exact_batch(const StepArgs& a, ExactCtx& c, Pair
         ++cnt.early;
         continue;
       }
-      if (pair_decision<MIXED>(a, c.ser64, c.ser32, o, st.chi, st.pref, cnt, &r1)) {
+      if (pair_decision<MIXED>(a, *c.mt, c.ser64, c.ser32, o, st.chi, st.pref, cnt, &r1)) {
         pair = true;
         kpair = k;
         done = k + 1;
@@ -1679,7 +1745,7 @@ __device__ __forceinline__ void exact_batch_runs(const StepArgs& a, ExactCtx& c,
       if (live) {
         const uint4 o = draw_words(q.id, q.seed, c.step, sc, kDraw);
         if (!below_bound<MIXED>(o, q.st.pbound)) ++cnt.early;
-        else make = pair_decision<MIXED>(a, c.ser64, c.ser32, o, q.st.chi, q.st.pref, cnt, &r1);
+        else make = pair_decision<MIXED>(a, *c.mt, c.ser64, c.ser32, o, q.st.chi, q.st.pref, cnt, &r1);
         m += make;
       }
       exact_append<FMODE>(a, c, ps, cnt, wc, make, q.x, q.kv, r1, wc_run, q.id, sc, q.inst, tau,
@@ -1709,12 +1775,15 @@ __device__ __forceinline__ void exact_pass(const StepArgs& a) {
   __shared__ BlockStats bs;
   __shared__ PairStage pstage[kWavesPerBlock];
   __shared__ double sbound[kBoundEntries];
+  __shared__ MathTab mt;
   WorkHdr* hdr = a.hdr;
   block_stats_init(bs);
   stage_bounds<MIXED>(a, sbound);
+  if (!MIXED) stage_math(mt);  // (the FP32 rates use the hardware's log2 and exp)
   __syncthreads();
   ExactCtx c;
   c.bound = sbound;
+  c.mt = &mt;
   c.ser64 = {a.tables->series[0], a.tables->series[1], a.tables->series[2], a.tables->series[3],
              a.tables->series[4]};
   c.ser32 = {(float)c.ser64.b0, (float)c.ser64.b1, (float)c.ser64.c0, (float)c.ser64.c1,
@@ -2142,9 +2211,9 @@ template <bool MIXED, int FMODE, bool RUNS>
 __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArgs& q,
                                                  GenWave& gw, int V,
                                                  const typename TabType<MIXED>::T* tab,
-                                                 const Series64& ser64, const Series32& ser32,
-                                                 BlockStats& bs, LaneCounters& cnt,
-                                                 WaveCounters& wc) {
+                                                 const MathTab& mt, const Series64& ser64,
+                                                 const Series32& ser32, BlockStats& bs,
+                                                 LaneCounters& cnt, WaveCounters& wc) {
   const ChildArena& A = q.iqa;
   const ChildArena& O = q.opa;
   const uint64_t below = lanes_below();
@@ -2152,10 +2221,13 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
   GenStream st;
   st.init(A, gw.wid, V, true);
   long long slot = -1;
-  int sp = 0, inst = 0, left = 0, k = 0;
-  V3 x{}, p{}, E{}, B{};
+  int sp = 0, inst = 0;
+  LepLane L;
+  V3 &x = L.x, &p = L.p, &E = L.E, &B = L.B;
+  int &k = L.k, &left = L.left;
+  double &h = L.h;
   uint64_t id = 0, seed = 0;
-  double wgt = 0.0, h = 0.0, dtfac = 0.0, qh2 = 0.0, hs3 = 0.0;
+  double wgt = 0.0;
   uint32_t nev = 0;
   const bool refine = a.forced <= 0 && a.adaptive;
   while (true) {
@@ -2184,23 +2256,22 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
           nev = ne ? ne[sl] : 0u;
           seed = a.inst[inst].seed;
           inherited_fields<FMODE>(a, A, r, inst, E, B);
-          const double g = sqrt(1.0 + dot(p, p));
-          const double chi = chi_of(p, g, E, FMODE == kFieldE ? V3{0.0, 0.0, 0.0} : B, a.eps_r);
+          const Kin kn = kin_of<FMODE != kFieldE>(p, E, B);
           int nsub = 1;
           if (a.forced > 0) {
             nsub = a.forced;
-          } else if (a.adaptive && chi > 0.0) {
+          } else if (a.adaptive && kn.c2 > 0.0) {
             const NsubInfo ni =
-                nsub_from_ratio(substep_ratio_lepton(tau, chi, g, a.inv_lep_scale));
+                nsub_from_ratio(substep_ratio_lepton(mt, tau, kn, a.eps_r, a.inv_lep_scale));
             nsub = ni.n;
             if (ni.near_int) block_count(bs, kPfNearInt);
             if (ni.clamped) block_count(bs, kPfClamped);
           }
-          if (!isfinite(chi)) block_count(bs, kPfNonfinite);
-          h = tau / (double)nsub;
-          dtfac = h * a.dtfac_per_h;
-          qh2 = (sp == QED_ELECTRON ? -0.5 : 0.5) * h;
-          hs3 = substep_cube(h, a.inv_lep_scale);
+          if (!isfinite(kn.c2)) block_count(bs, kPfNonfinite);
+          h = div_normal(tau, (double)nsub, rcp_normal((double)nsub));
+          L.dtfac = h * a.dtfac_per_h;
+          L.qh2 = (sp == QED_ELECTRON ? -0.5 : 0.5) * h;
+          L.hs3 = a.eps_r * a.eps_r * substep_cube(h, a.inv_lep_scale);
           k = 0;
           left = nsub;
           slot = sl;
@@ -2211,31 +2282,13 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
     }
     if (wave_ballot(slot >= 0) == 0) break;
 
-    // ---- one sub-step (taken again at half the length if its end state breaks Eq. (29)) ----
-    double g = 1.0, chi = 0.0;
+    // ---- one sub-step, with the first run of the emission generator ----
+    Kin kn{0.0, 0.0, {1.0, 1.0, true}};
+    bool first = false;
+    double delta1 = 0.0;
     if (slot >= 0) {
-      const V3 p0 = p;
-      for (;;) {
-        if (FMODE == kFieldE) {
-          p = {p0.x + 2.0 * qh2 * E.x, p0.y + 2.0 * qh2 * E.y, p0.z + 2.0 * qh2 * E.z};
-        } else {
-          p = p0;
-          boris(p, qh2, E, B);
-        }
-        const double p2 = dot(p, p);
-        g = sqrt(1.0 + p2);
-        chi = chi_of(p, g, E, FMODE == kFieldE ? V3{0.0, 0.0, 0.0} : B, a.eps_r);
-        if (!(refine && chi > 0.0) ||
-            !refine_substep(hs3, chi, p2, g, h, a.inv_lep_scale, k, left, bs))
-          break;
-        h *= 0.5;
-        qh2 *= 0.5;
-        dtfac *= 0.5;
-        hs3 *= 0.125;
-        left *= 2;
-      }
-      const double hg = h / g;
-      x = {x.x + hg * p.x, x.y + hg * p.y, x.z + hg * p.z};
+      first = lepton_substep<MIXED, FMODE != kFieldE>(a, tab, mt, ser64, ser32, id, seed, step,
+                                                      refine, L, kn, bs, cnt, delta1);
       ++cnt.subs;
     }
     // the emission generator, N_g times in the reverse mode of Sec. VI (as in lepton_kernel)
@@ -2248,11 +2301,15 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
       bool emit = false;
       double f = 0.0;
       if (slot >= 0 && a.emission) {
-        const uint4 o = draw_words(id, seed, step, sc, kDraw);
-        double delta;
-        emit = emission_decision<MIXED>(tab, ser64, ser32, o, chi, g, dtfac, cnt, delta);
+        double delta = delta1;
+        if (run == 0)
+          emit = first;
+        else
+          emit = emission_decision<MIXED>(
+              tab, mt, ser64, ser32, emission_draw<MIXED>(draw_words(id, seed, step, sc, kDraw)),
+              kn, a.eps_r, a.inv_eps_r, L.dtfac, cnt, delta);
         if (emit) {
-          emit = emission_photon(p, g, delta, wrun, bs, cnt, f);
+          emit = emission_photon(mt, kn, delta, wrun, bs, cnt, f);
           if (emit) ++nev;
         }
       }
@@ -2307,7 +2364,7 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
       if (emit) {
         // recoil: the lepton keeps p - k (momentum conservation, Sec. IV.F)
         if (runs == 1) {
-          p = {p.x - f * p.x, p.y - f * p.y, p.z - f * p.z};
+          p = recoil(p, f);
         } else {
           rec = {rec.x + f * p.x, rec.y + f * p.y, rec.z + f * p.z};
           fired = true;
@@ -2336,10 +2393,10 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
 // the leptons).
 template <bool MIXED, int FMODE, bool RUNS>
 __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArgs& q,
-                                                 GenWave& gw, int V, const Series64& ser64,
-                                                 const Series32& ser32, BlockStats& bs,
-                                                 LaneCounters& cnt, LaneCounters& pcnt,
-                                                 WaveCounters& wc) {
+                                                 GenWave& gw, int V, const MathTab& mt,
+                                                 const Series64& ser64, const Series32& ser32,
+                                                 BlockStats& bs, LaneCounters& cnt,
+                                                 LaneCounters& pcnt, WaveCounters& wc) {
   const ChildArena& A = q.ipa;
   const ChildArena& O = q.oqa;
   const uint64_t below = lanes_below();
@@ -2372,15 +2429,15 @@ __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArg
           id = S.id[sl];
           x = {S.x[sl], S.y[sl], S.z[sl]};
           kv = {S.px[sl], S.py[sl], S.pz[sl]};
-          const double kabs = sqrt(dot(kv, kv));
+          const Root kr = root_of(dot(kv, kv));
+          const double kabs = kr.r, inv_k = kr.under(1.0);
           if (!(kabs > 0.0) || !isfinite(kabs)) {
             block_count(bs, kPfNonfinite);
           } else {
             inst = (int)A.inst[r];
             seed = a.inst[inst].seed;
             inherited_fields<FMODE>(a, A, r, inst, E, B);
-            const double inv_k = 1.0 / kabs;
-            chi = chi_of(kv, kabs, E, B, a.eps_r);
+            chi = a.eps_r * root_of(chi_sq<FMODE != kFieldE>(kv, kabs, E, B)).r;
             nsub = 1;
             if (a.forced > 0) {
               nsub = a.forced;
@@ -2392,7 +2449,7 @@ __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArg
               if (ni.clamped) block_count(bs, kPfClamped);
             }
             if (!isfinite(chi)) block_count(bs, kPfNonfinite);
-            h = nsub == 1 ? tau : tau / (double)nsub;
+            h = nsub == 1 ? tau : div_normal(tau, (double)nsub, rcp_normal((double)nsub));
             hk = h * inv_k;
             pref = h * (a.dtfac_per_h * kInvSqrt3Pi) * inv_k;
             wcur = S.w[sl];
@@ -2421,7 +2478,7 @@ __device__ __forceinline__ void gen_photon_phase(const StepArgs& a, const GenArg
       double r1 = 0.0, wp = 0.0;
       if (slot >= 0 && a.pairs) {
         const uint4 o = draw_words(id, seed, step, sc, kDraw);
-        if (pair_decision<MIXED>(a, ser64, ser32, o, chi, pref, pcnt, &r1)) {
+        if (pair_decision<MIXED>(a, mt, ser64, ser32, o, chi, pref, pcnt, &r1)) {
           ++m;
           // the photon decays; its pair is created with probability 1 / f_g, or for one
           // photon in f_g in the deterministic form (Sec. VI)
@@ -2521,6 +2578,7 @@ __device__ __forceinline__ void gen_pass(const StepArgs& a, const GenArgs& q) {
   using Tab = typename TabType<MIXED>::T;
   __shared__ BlockStats bs;
   __shared__ Tab tab[kTableN];  // the emission table, as in the lepton kernel
+  __shared__ MathTab mt;
   // a workgroup without a child writes its empty counts (only the first pass stores its
   // statistics; the scan takes a generation without children at all as empty)
   const unsigned np = q.ipa.waves > 0 ? q.ipa.used[1] : 0u;
@@ -2540,6 +2598,7 @@ __device__ __forceinline__ void gen_pass(const StepArgs& a, const GenArgs& q) {
     return;
   }
   block_stats_init(bs);
+  stage_math(mt);
   {
     const Tab* src = MIXED ? reinterpret_cast<const Tab*>(a.tables->ab32)
                            : reinterpret_cast<const Tab*>(a.tables->ab64);
@@ -2559,8 +2618,8 @@ __device__ __forceinline__ void gen_pass(const StepArgs& a, const GenArgs& q) {
   pcnt.bs = &bs;
   WaveCounters wc;
   // photons of the previous generation, then its electrons and positrons
-  gen_photon_phase<MIXED, FMODE, RUNS>(a, q, gw, V, ser64, ser32, bs, cnt, pcnt, wc);
-  gen_lepton_phase<MIXED, FMODE, RUNS>(a, q, gw, V, tab, ser64, ser32, bs, cnt, wc);
+  gen_photon_phase<MIXED, FMODE, RUNS>(a, q, gw, V, mt, ser64, ser32, bs, cnt, pcnt, wc);
+  gen_lepton_phase<MIXED, FMODE, RUNS>(a, q, gw, V, tab, mt, ser64, ser32, bs, cnt, wc);
   if (q.opa.waves > 0) {
     gw.tp.flush(q.opa, gw.wid);
     if (lane == 0) q.opa.nrec[gw.wid] = (unsigned)gw.cp.n;
