@@ -339,6 +339,7 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   const int lep_waves = lep.grid * (block / 64);
   const int pho_waves = pho.grid * (block / 64);
   a.pho_waves = run_photons ? pho_waves : 0;
+  a.wpb = block / 64;
   a.cand_per_wave = cand_list_entries(stores->slots[QED_PHOTON], pho_waves);
   if (arena > 0) {
     const bool on = G > 0;

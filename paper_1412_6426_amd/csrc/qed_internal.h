@@ -31,8 +31,8 @@ inline long long cand_list_entries(long long photon_slots, int pho_waves) {
   return pho_waves > 0 ? (slots + (long long)kMaxWaves * kCandSlack) / pho_waves : 0;
 }
 
-// Per-workgroup partial stats: 64-bit words, stored field-major ([field][block]) so that
-// the finalize kernel reduces each field with coalesced loads.
+// Per-workgroup partial stats: 64-bit words, stored in groups of eight fields
+// ([group][block][field]), so that a workgroup's stores and the reduction's loads are whole lines.
 enum PartialField : int {
   kPfSubsteps = 0, kPfEvents, kPfSaturated, kPfNear, kPfNonfinite, kPfNearInt, kPfClamped,
   kPfDropped, kPfEarly, kPfAdv0, kPfAdv1, kPfWaveIters, kPfLowOcc,
@@ -363,6 +363,7 @@ struct StepArgs {
   int gen_grid;
   int lep_grid, pho_grid, ex_grid;  // workgroups of the lepton, photon and exact-pair kernels
   int pho_waves;                    // wavefronts of the photon kernel
+  int wpb;                          // wavefronts per workgroup of the lepton and photon kernels
   qed_stats* stats;
   long long* d_step;
   hipEvent_t events[4];

@@ -62,15 +62,15 @@ __device__ __forceinline__ long long chunk_size(long long N, long long W, long l
   if (tile > 0) return tile;
   if (N >= kDefaultTile * W) return kDefaultTile;
   if (spread <= 0 || N >= 64 * spread) return 64;
-  const long long t = (N + spread - 1) / spread;
-  return t < 1 ? 1 : t;
+  const unsigned t = ((unsigned)N + (unsigned)spread - 1u) / (unsigned)spread;
+  return t < 1u ? 1 : (long long)t;
 }
 
 // ------------------------------------------------------------------------------------
 // prep / finalize
 // ------------------------------------------------------------------------------------
+constexpr int kPrepWaves = 4;  // workgroups of 256
 __global__ void __launch_bounds__(256) prep_kernel(StepArgs a, int run_photons) {
-  __shared__ int s_ok;
   if (blockIdx.x > 0) {
     // workgroups 1.. clear the per-(instance, wavefront) child counts of the arenas and
     // their pool counters
@@ -88,65 +88,97 @@ __global__ void __launch_bounds__(256) prep_kernel(StepArgs a, int run_photons) 
     }
     return;
   }
+  // Instance by instance per thread: the counts, the fields, and a workgroup scan of the
+  // counts into the prefixes (64 instances: 10.4 us a launch, 28.4 with one thread walking them).
+  __shared__ long long wl[kPrepWaves], wp[kPrepWaves];
+  __shared__ long long s_ns[3];
   WorkHdr* hdr = a.hdr;
   const long long n = *a.d_step;
   const double tn = a.t0 + (double)n * a.dt;
-  if (threadIdx.x == 0) s_ok = (a.tables->magic == kTableMagic) ? 1 : 0;
-  __syncthreads();
-  const int ok = s_ok;
-  for (int i = threadIdx.x; i < a.n_inst; i += blockDim.x) {
-    qed_instance& I = a.inst[i];
-    if (a.freeze_on_drop && I.dropped > 0) I.frozen = 1;
-    for (int s = 0; s < 3; ++s) {
-      long long c = I.count[s];
-      if (c > I.capacity[s]) c = I.capacity[s];
-      if (c < 0) c = 0;
-      I.count[s] = c;
-      a.n0[i * 3 + s] = (I.frozen || !ok) ? 0 : c;
-    }
-    double* eb = a.eb + 6 * i;
-    const double amp = I.amp;
-    if (a.field.kind == QED_FIELD_UNIFORM) {
-      for (int d = 0; d < 3; ++d) {
-        eb[d] = a.e0[d] * amp;
-        eb[3 + d] = a.b0[d] * amp;
-      }
-    } else if (a.field.kind == QED_FIELD_ROTATING_E) {
-      double sph, cph;
-      sincos(a.field.omega * tn + a.field.phase, &sph, &cph);
-      const double e = a.field.amp * amp;
-      eb[0] = e * cph;
-      eb[1] = e * sph;
-      eb[2] = eb[3] = eb[4] = eb[5] = 0.0;
-    }
-  }
+  const bool ok = a.tables->magic == kTableMagic;
+  const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
   unsigned long long* sw = reinterpret_cast<unsigned long long*>(a.stats);
   for (int w = threadIdx.x; w < (int)(sizeof(qed_stats) / 8); w += blockDim.x) sw[w] = 0ull;
+  if (threadIdx.x < 3) s_ns[threadIdx.x] = 0;
+  __syncthreads();
+  long long carry_l = 0, carry_p = 0, ns[3] = {0, 0, 0};
+  for (int i0 = 0; i0 < a.n_inst; i0 += (int)blockDim.x) {
+    const int i = i0 + (int)threadIdx.x;
+    long long live[3] = {0, 0, 0};
+    if (i < a.n_inst) {
+      qed_instance& I = a.inst[i];
+      if (a.freeze_on_drop && I.dropped > 0) I.frozen = 1;
+      const bool off = I.frozen || !ok;
+      for (int s = 0; s < 3; ++s) {
+        long long c = I.count[s];
+        if (c > I.capacity[s]) c = I.capacity[s];
+        if (c < 0) c = 0;
+        I.count[s] = c;
+        live[s] = off ? 0 : c;
+        a.n0[i * 3 + s] = live[s];
+        ns[s] += live[s];
+      }
+      double* eb = a.eb + 6 * i;
+      const double amp = I.amp;
+      if (a.field.kind == QED_FIELD_UNIFORM) {
+        for (int d = 0; d < 3; ++d) {
+          eb[d] = a.e0[d] * amp;
+          eb[3 + d] = a.b0[d] * amp;
+        }
+      } else if (a.field.kind == QED_FIELD_ROTATING_E) {
+        double sph, cph;
+        sincos(a.field.omega * tn + a.field.phase, &sph, &cph);
+        const double e = a.field.amp * amp;
+        eb[0] = e * cph;
+        eb[1] = e * sph;
+        eb[2] = eb[3] = eb[4] = eb[5] = 0.0;
+      }
+    }
+    // inclusive scans over the workgroup's threads of the lepton and photon counts
+    long long xl = live[0] + live[1], xp = run_photons ? live[2] : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const long long yl = __shfl_up(xl, o, 64), yp = __shfl_up(xp, o, 64);
+      if (lane >= o) {
+        xl += yl;
+        xp += yp;
+      }
+    }
+    if (lane == 63) {
+      wl[wv] = xl;
+      wp[wv] = xp;
+    }
+    __syncthreads();
+    long long bl = carry_l, bp = carry_p;
+    for (int q = 0; q < kPrepWaves; ++q) {
+      if (q < wv) {
+        bl += wl[q];
+        bp += wp[q];
+      }
+      carry_l += wl[q];
+      carry_p += wp[q];
+    }
+    __syncthreads();
+    if (i < a.n_inst) {
+      a.lep_pref[2 * i + 2] = bl + xl;
+      a.lep_pref[2 * i + 1] = bl + xl - live[1];
+      a.pho_pref[i + 1] = bp + xp;
+    }
+  }
+  for (int s = 0; s < 3; ++s)
+    if (ns[s]) atomicAdd(reinterpret_cast<unsigned long long*>(&s_ns[s]), (unsigned long long)ns[s]);
   __syncthreads();
   if (threadIdx.x == 0) {
-    long long lp = 0, pp = 0, ns[3] = {0, 0, 0};
     a.lep_pref[0] = 0;
     a.pho_pref[0] = 0;
-    for (int i = 0; i < a.n_inst; ++i) {
-      for (int s = 0; s < 2; ++s) {
-        const long long c = a.n0[i * 3 + s];
-        lp += c;
-        a.lep_pref[2 * i + s + 1] = lp;
-        ns[s] += c;
-      }
-      const long long c = a.n0[i * 3 + 2];
-      if (run_photons) pp += c;
-      a.pho_pref[i + 1] = pp;
-      ns[2] += c;
-    }
-    hdr->lep_total = lp;
-    hdr->pho_total = pp;
+    hdr->lep_total = carry_l;
+    hdr->pho_total = carry_p;
     hdr->n_cand = 0ull;
     hdr->step = n;
     hdr->tn = tn;
-    hdr->tables_ok = (uint32_t)ok;
+    hdr->tables_ok = ok ? 1u : 0u;
     a.stats->step = n;
-    for (int s = 0; s < 3; ++s) a.stats->n_start[s] = ns[s];
+    for (int s = 0; s < 3; ++s) a.stats->n_start[s] = s_ns[s];
     if (!ok) a.stats->status = QED_STATUS_NO_TABLES;
   }
 }
@@ -155,60 +187,97 @@ __device__ __forceinline__ void stats_add(int64_t* p, unsigned long long v) {
   if (v) atomicAdd(reinterpret_cast<unsigned long long*>(p), v);
 }
 
-// Partial-stats reduction: one wavefront per (partial set, field).  The lepton and
-// generation sets have all kPfCount fields; the photon and exact-pair sets only the
-// counters below kPfNsub (their histogram fields stay zero).  Sums go into the zeroed stats
-// record with atomics.
-constexpr int kReduceJobs = 2 * kPfCount + 2 * kPfNsub;
-constexpr int kReduceBlocks = (kReduceJobs + 3) / 4;  // workgroups of 4 wavefronts
+// Where field f of workgroup b's partial record sits: in groups of kPfGroup fields, the group's
+// fields of one workgroup side by side (64 bytes) and the workgroups in turn, so that a
+// workgroup stores whole lines and the reduction reads them (a row per field left every
+// workgroup 182 stores to as many lines).  The last group is as wide as what is left.
+constexpr int kPfGroup = 8;
+__device__ __forceinline__ size_t part_index(int f, int b) {
+  const int g = f / kPfGroup, w = kPfCount - g * kPfGroup < kPfGroup ? kPfCount - g * kPfGroup : kPfGroup;
+  return (size_t)g * kPfGroup * kMaxGridBlocks + (size_t)b * w + (size_t)(f - g * kPfGroup);
+}
+
+// Partial-stats reduction: one wavefront per (partial set, group of fields, slice of
+// kPfSlice workgroups).  The lepton and generation sets have all kPfCount fields; the photon
+// and exact-pair sets only the counters below kPfNsub.  Lane l takes field l % 8 of every
+// eighth workgroup of the slice, kPfSlice / 8 independent loads (a wavefront per group over all
+// workgroups waited for 256 loads in turn: 36 us a launch against 9.5).  Sums go into the zeroed
+// stats record with atomics.
+constexpr int kPfSlice = 128;
+constexpr int kGroupsAll = (kPfCount + kPfGroup - 1) / kPfGroup;
+constexpr int kGroupsCount = (kPfNsub + kPfGroup - 1) / kPfGroup;
+__host__ __device__ inline int pf_slices(int grid) { return (grid + kPfSlice - 1) / kPfSlice; }
+// Jobs of set `kind` (0 leptons, 1 photons, 2 exact pairs, 3 generations), and of all four.
+__host__ __device__ inline int reduce_jobs_of(const StepArgs& a, int kind) {
+  return kind == 0   ? kGroupsAll * pf_slices(a.lep_grid)
+         : kind == 1 ? kGroupsCount * pf_slices(a.pho_grid)
+         : kind == 2 ? kGroupsCount * pf_slices(a.ex_grid)
+                     : kGroupsAll * pf_slices(a.gen_grid);
+}
+inline int reduce_blocks(const StepArgs& a) {  // workgroups of 4 wavefronts
+  int n = 0;
+  for (int kind = 0; kind < 4; ++kind) n += reduce_jobs_of(a, kind);
+  return (n + 3) / 4;
+}
+
+__device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, long long tile,
+                                              long long spread);
 
 __device__ __forceinline__ void reduce_job(const StepArgs& a, int job, int lane) {
-  if (job >= kReduceJobs) return;
-  int kind, f;  // kind 0 leptons, 1 photons, 2 exact pairs, 3 generations
-  if (job < kPfCount) {
-    kind = 0;
-    f = job;
-  } else if (job < kPfCount + 2 * kPfNsub) {
-    kind = 1 + (job - kPfCount) / kPfNsub;
-    f = (job - kPfCount) % kPfNsub;
-  } else {
-    kind = 3;
-    f = job - kPfCount - 2 * kPfNsub;
-  }
+  int kind = 0;
+  while (kind < 4 && job >= reduce_jobs_of(a, kind)) job -= reduce_jobs_of(a, kind++);
+  if (kind == 4) return;
+  const int groups = kind == 0 || kind == 3 ? kGroupsAll : kGroupsCount;
+  const int g = job % groups, b0 = (job / groups) * kPfSlice;
   const bool pho = kind == 1 || kind == 2;
-  const int G = kind == 0 ? a.lep_grid
-                          : (kind == 1 ? a.pho_grid : (kind == 2 ? a.ex_grid : a.gen_grid));
-  if (G <= 0) return;
+  // the workgroups that have stored a record: idle ones of the lepton and photon kernels do not
+  const int G = kind == 0   ? working_blocks(a.hdr->lep_total, a.lep_grid, a.wpb, a.tile, a.spread)
+                : kind == 1 ? working_blocks(a.hdr->pho_total, a.pho_grid, a.wpb, a.tile, 0)
+                : kind == 2 ? a.ex_grid
+                            : a.gen_grid;
+  if (b0 >= G) return;
   const unsigned long long* part =
       kind == 0 ? a.lep_part : (kind == 1 ? a.pho_part : (kind == 2 ? a.ex_part : a.gen_part));
-  const unsigned long long* col = part + (size_t)f * kMaxGridBlocks;
+  const int f = g * kPfGroup + (lane & (kPfGroup - 1));
+  const bool mine = f < (pho ? kPfNsub : kPfCount);
+  const bool sumd = f == kPfEnergy, maxd = f == kPfMaxP || f == kPfMaxQ;
   qed_stats* st = a.stats;
-  if (f == kPfEnergy || f == kPfMaxP || f == kPfMaxQ) {
-    double v = 0.0;
-    for (int b = lane; b < G; b += 64) {
-      const double x = __longlong_as_double((long long)col[b]);
-      v = (f == kPfEnergy) ? v + x : fmax(v, x);
+  unsigned long long v = 0ull;
+  double d = 0.0;
+  if (mine) {
+    constexpr int kLoads = kPfSlice * kPfGroup / 64;
+    unsigned long long xs[kLoads];
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      const int b = b0 + lane / kPfGroup + q * (64 / kPfGroup);
+      xs[q] = b < G ? part[part_index(f, b)] : 0ull;
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const double y = __shfl_xor(v, o, 64);
-      v = (f == kPfEnergy) ? v + y : fmax(v, y);
+    for (int q = 0; q < kLoads; ++q) {
+      const unsigned long long x = xs[q];
+      if (sumd) d += __longlong_as_double((long long)x);
+      else if (maxd) d = fmax(d, __longlong_as_double((long long)x));
+      else v += x;
     }
-    if (lane == 0 && v != 0.0) {
-      if (f == kPfEnergy) {
-        if (!pho) atomicAdd(&st->photon_energy, v);
+  }
+#pragma unroll
+  for (int o = 32; o >= kPfGroup; o >>= 1) {
+    v += __shfl_xor(v, o, 64);
+    const double y = __shfl_xor(d, o, 64);
+    d = sumd ? d + y : fmax(d, y);
+  }
+  if (lane >= kPfGroup || !mine) return;
+  if (sumd || maxd) {
+    if (d != 0.0) {
+      if (sumd) {
+        if (!pho) atomicAdd(&st->photon_energy, d);
       } else {
-        atomic_max_nonneg((pho || f == kPfMaxQ) ? &st->max_p_pair : &st->max_p_emit, v);
+        atomic_max_nonneg((pho || f == kPfMaxQ) ? &st->max_p_pair : &st->max_p_emit, d);
       }
     }
     return;
   }
-  unsigned long long v = 0ull;
-#pragma unroll 4
-  for (int b = lane; b < G; b += 64) v += col[b];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if (lane != 0 || v == 0ull) return;
+  if (v == 0ull) return;
   switch (f) {
     case kPfSubsteps: stats_add(&st->substeps, v); break;
     case kPfEvents: stats_add(pho ? &st->pairs : &st->emitted, v); break;
@@ -391,14 +460,15 @@ __device__ void wave_to_block(BlockStats& bs, const LaneCounters& c, const WaveC
   }
 }
 
-// After a __syncthreads: store the workgroup's record as column blockIdx.x of `part`.
-__device__ __forceinline__ void block_stats_store(const BlockStats& bs, unsigned long long* part) {
-  for (int i = threadIdx.x; i < kPfCount; i += blockDim.x) {
+// After a __syncthreads: store the first `fields` fields of the workgroup's record.
+__device__ __forceinline__ void block_stats_store(const BlockStats& bs, unsigned long long* part,
+                                                  int fields) {
+  for (int i = threadIdx.x; i < fields; i += blockDim.x) {
     unsigned long long v = bs.w[i];
     if (i == kPfEnergy) v = (unsigned long long)__double_as_longlong(bs.energy);
     if (i == kPfMaxP) v = (unsigned long long)__double_as_longlong(bs.maxp);
     if (i == kPfMaxQ) v = (unsigned long long)__double_as_longlong(bs.maxq);
-    part[(size_t)i * kMaxGridBlocks + blockIdx.x] = v;
+    part[part_index(i, (int)blockIdx.x)] = v;
   }
 }
 
@@ -406,7 +476,7 @@ __device__ __forceinline__ void block_stats_store(const BlockStats& bs, unsigned
 __device__ __forceinline__ void block_stats_accumulate(const BlockStats& bs,
                                                        unsigned long long* part, bool first) {
   for (int i = threadIdx.x; i < kPfCount; i += blockDim.x) {
-    const size_t at = (size_t)i * kMaxGridBlocks + blockIdx.x;
+    const size_t at = part_index(i, (int)blockIdx.x);
     const unsigned long long old = first ? 0ull : part[at];
     unsigned long long v;
     if (i == kPfEnergy) {
@@ -645,11 +715,26 @@ struct WaveRange {
   }
 };
 
-// Does this workgroup own any work?  (its first wavefront's first chunk starts below N)
+// Wavefronts of a kernel of W that own any of N particles (the first ones), and workgroups.
+__device__ __forceinline__ long long working_waves(long long N, long long W, long long tile,
+                                                   long long spread) {
+  const long long T = chunk_size(N, W, tile, spread);
+  // (a 64-bit division costs every workgroup of a launch 0.1 us)
+  const long long n = T == kDefaultTile        ? (N + (kDefaultTile - 1)) / kDefaultTile
+                      : T == 64                ? (N + 63) / 64
+                      : N < (1ll << 31) - T    ? (long long)(((unsigned)N + (unsigned)T - 1u) / (unsigned)T)
+                                               : (N + T - 1) / T;
+  return n < W ? n : W;
+}
+__device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, long long tile,
+                                              long long spread) {
+  return grid > 0 ? (int)((working_waves(N, (long long)grid * wpb, tile, spread) + wpb - 1) / wpb)
+                  : 0;
+}
+// Does this workgroup own any work?
 __device__ __forceinline__ bool block_has_work(long long N, long long tile, long long spread) {
-  const long long wpb = blockDim.x >> 6;
-  return (long long)blockIdx.x * wpb *
-             chunk_size(N, (long long)gridDim.x * wpb, tile, spread) < N;
+  return (int)blockIdx.x <
+         working_blocks(N, (int)gridDim.x, (int)(blockDim.x >> 6), tile, spread);
 }
 
 template <bool MIXED>
@@ -926,13 +1011,11 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->lep_total;
   const int wid = wave_index();
-  block_stats_init(bs);
   if (!block_has_work(N, a.tile, a.spread)) {
     if (a.pa.waves > 0 && lane_id() == 0) a.pa.nrec[wid] = 0u;
-    __syncthreads();
-    block_stats_store(bs, a.lep_part);
     return;
   }
+  block_stats_init(bs);
   const Tab* src = MIXED ? reinterpret_cast<const Tab*>(a.tables->ab32)
                          : reinterpret_cast<const Tab*>(a.tables->ab64);
   if (!kGlobalTab)
@@ -1229,7 +1312,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
 
   wave_to_block(bs, cnt, wc);
   __syncthreads();
-  block_stats_store(bs, a.lep_part);
+  block_stats_store(bs, a.lep_part, kPfCount);
 }
 
 template <bool MIXED, int FMODE, bool EXT>
@@ -1395,14 +1478,10 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->pho_total;
   const int wid = wave_index();
+  if (!block_has_work(N, a.tile, 0)) return;
   block_stats_init(bs);
   stage_bounds<MIXED>(a, sbound);
   __syncthreads();
-  if (!block_has_work(N, a.tile, 0)) {
-    if (lane_id() == 0) a.candn[wid] = 0u;
-    block_stats_store(bs, a.pho_part);
-    return;
-  }
   const uint32_t step = (uint32_t)hdr->step;
   FieldArgs fld = a.field;
   fld.tn = hdr->tn;
@@ -1525,7 +1604,7 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   if (lane == 0) a.candn[wid] = (unsigned)ncand;
   wave_to_block(bs, cnt, wc);
   __syncthreads();
-  block_stats_store(bs, a.pho_part);
+  block_stats_store(bs, a.pho_part, kPfNsub);
 }
 
 // State of one wavefront of the exact pair-decision kernel.
@@ -1640,21 +1719,19 @@ __device__ __forceinline__ ExactCand load_candidate(const StepArgs& a, const Exa
   return q;
 }
 
-// Exact pair decision for the candidates list[i0 + lane] (i0 + lane < n); all lanes call.
+// Exact pair decision for the candidate `entry` of each lane that has one; all lanes call.
 template <bool MIXED, int FMODE>
 __device__ __forceinline__ void exact_batch(const StepArgs& a, ExactCtx& c, PairStage& ps,
-                                            LaneCounters& cnt, WaveCounters& wc,
-                                            const unsigned long long* list, long long i0,
-                                            long long n) {
+                                            LaneCounters& cnt, WaveCounters& wc, bool has,
+                                            unsigned long long entry) {
   const qed_soa& S = a.sp[QED_PHOTON];
-  const long long i = i0 + lane_id();
   bool pair = false, make = false;
   double r1 = 0.0, wp = 0.0, tau = 0.0;
   int kpair = 0, inst = 0, nsub = 0;
   V3 x{}, kv{}, Ef{}, Bf{};
   uint64_t id = 0;
-  if (i < n) {
-    const ExactCand q = load_candidate<MIXED, FMODE>(a, c, list[i]);
+  if (has) {
+    const ExactCand q = load_candidate<MIXED, FMODE>(a, c, entry);
     const PhotonSetup& st = q.st;
     const long long s = q.s;
     inst = q.inst;
@@ -1710,18 +1787,16 @@ __device__ __forceinline__ void exact_batch(const StepArgs& a, ExactCtx& c, Pair
 // N_g fire.  Pairs are appended run by run, so a photon can make several.
 template <bool MIXED, int FMODE>
 __device__ __forceinline__ void exact_batch_runs(const StepArgs& a, ExactCtx& c, PairStage& ps,
-                                                 LaneCounters& cnt, WaveCounters& wc,
-                                                 const unsigned long long* list, long long i0,
-                                                 long long n) {
+                                                 LaneCounters& cnt, WaveCounters& wc, bool has,
+                                                 unsigned long long entry) {
   const qed_soa& S = a.sp[QED_PHOTON];
-  const long long i = i0 + lane_id();
   const int R = a.runs_pair;
-  bool live = i < n;
+  bool live = has;
   ExactCand q{};
   int k = 0;
   double wcur = 0.0;
   if (live) {
-    q = load_candidate<MIXED, FMODE>(a, c, list[i]);
+    q = load_candidate<MIXED, FMODE>(a, c, entry);
     // the sub-steps before kc were settled by the bound: only the push remains
     if (a.push_photons)
       for (; k < q.kc; ++k)
@@ -1770,13 +1845,49 @@ __device__ __forceinline__ void exact_batch_runs(const StepArgs& a, ExactCtx& c,
   }
 }
 
+// Candidate lists of one workgroup at most (the lists of kMaxWaves photon wavefronts over
+// kExactGridBlocks workgroups); one wavefront scans their counts.
+constexpr int kExactLists = (kMaxWaves + kExactGridBlocks - 1) / kExactGridBlocks;
+static_assert(kExactLists < 64, "one wavefront scans a workgroup's list counts");
+
 template <bool MIXED, int FMODE, bool RUNS>
 __device__ __forceinline__ void exact_pass(const StepArgs& a) {
   __shared__ BlockStats bs;
   __shared__ PairStage pstage[kWavesPerBlock];
   __shared__ double sbound[kBoundEntries];
   __shared__ MathTab mt;
+  __shared__ unsigned lfirst[kExactLists + 1];  // first candidate of each list of the workgroup
   WorkHdr* hdr = a.hdr;
+  const int wpb = (int)(blockDim.x >> 6);
+  // The photon kernel's per-wavefront lists are cut over the workgroups, and a workgroup's
+  // candidates are one index space, 64 at a time per wavefront: the lists hold a few each, and
+  // a wavefront that took list after list waited for the columns of each in turn (mixed
+  // cascade, 14.2 to 11.4 us a launch; 9.4 to 3 where there is no candidate).
+  const int lists = (int)working_waves(hdr->pho_total, a.pho_waves, a.tile, 0);
+  const int per = (lists + (int)gridDim.x - 1) / (int)gridDim.x;  // <= kExactLists
+  const int l0 = (int)blockIdx.x * per < lists ? (int)blockIdx.x * per : lists;
+  const int nl = l0 + per < lists ? per : lists - l0;
+  if (threadIdx.x < 64) {
+    const int l = (int)threadIdx.x;
+    const unsigned v = l < nl ? a.candn[l0 + l] : 0u;
+    unsigned x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned y = __shfl_up(x, o, 64);
+      if (l >= o) x += y;
+    }
+    if (l <= kExactLists) lfirst[l] = x - v;
+  }
+  __syncthreads();
+  const int n_lists = (int)lfirst[nl];
+  long long n_over = (long long)hdr->n_cand;  // the overflow list
+  if (n_over > a.cand_cap) n_over = a.cand_cap;
+  if (n_lists == 0 && n_over == 0) {
+    if (a.qa.waves > 0 && lane_id() == 0) a.qa.nrec[wave_index()] = 0u;
+    for (int i = threadIdx.x; i < kPfNsub; i += blockDim.x)
+      a.ex_part[part_index(i, (int)blockIdx.x)] = 0ull;
+    return;
+  }
   block_stats_init(bs);
   stage_bounds<MIXED>(a, sbound);
   if (!MIXED) stage_math(mt);  // (the FP32 rates use the hardware's log2 and exp)
@@ -1800,21 +1911,27 @@ __device__ __forceinline__ void exact_pass(const StepArgs& a) {
   WaveCounters wc;
   const int V = (int)gridDim.x * (int)(blockDim.x >> 6);
 
-  // the photon kernel's per-wavefront lists, one list per wavefront at a time
-  for (int sw = c.wid; sw < a.pho_waves; sw += V) {
-    const long long n = (long long)a.candn[sw];
-    const unsigned long long* list = a.candw + (size_t)sw * a.cand_per_wave;
-    for (long long i0 = 0; i0 < n; i0 += 64) {
-      if constexpr (RUNS) exact_batch_runs<MIXED, FMODE>(a, c, ps, cnt, wc, list, i0, n);
-      else exact_batch<MIXED, FMODE>(a, c, ps, cnt, wc, list, i0, n);
+  for (int i0 = (int)(threadIdx.x & ~63u); i0 < n_lists; i0 += wpb * 64) {
+    const int i = i0 + lane_id();
+    unsigned long long e = 0ull;
+    if (i < n_lists) {
+      int lo = 0, hi = nl;  // lfirst[lo] <= i < lfirst[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if ((int)lfirst[mid] <= i) lo = mid;
+        else hi = mid;
+      }
+      e = a.candw[(size_t)(l0 + lo) * a.cand_per_wave + (size_t)(i - (int)lfirst[lo])];
     }
+    if constexpr (RUNS) exact_batch_runs<MIXED, FMODE>(a, c, ps, cnt, wc, i < n_lists, e);
+    else exact_batch<MIXED, FMODE>(a, c, ps, cnt, wc, i < n_lists, e);
   }
   // then the overflow list
-  long long n = (long long)hdr->n_cand;
-  if (n > a.cand_cap) n = a.cand_cap;
-  for (long long i0 = (long long)c.wid * 64; i0 < n; i0 += (long long)V * 64) {
-    if constexpr (RUNS) exact_batch_runs<MIXED, FMODE>(a, c, ps, cnt, wc, a.cand, i0, n);
-    else exact_batch<MIXED, FMODE>(a, c, ps, cnt, wc, a.cand, i0, n);
+  for (long long i0 = (long long)c.wid * 64; i0 < n_over; i0 += (long long)V * 64) {
+    const bool has = i0 + lane_id() < n_over;
+    const unsigned long long e = has ? a.cand[i0 + lane_id()] : 0ull;
+    if constexpr (RUNS) exact_batch_runs<MIXED, FMODE>(a, c, ps, cnt, wc, has, e);
+    else exact_batch<MIXED, FMODE>(a, c, ps, cnt, wc, has, e);
   }
 
   if (c.staged > 0) flush_pairs(a, ps, c.staged, c.step, cnt);
@@ -1824,7 +1941,7 @@ __device__ __forceinline__ void exact_pass(const StepArgs& a) {
   }
   wave_to_block(bs, cnt, wc);
   __syncthreads();
-  block_stats_store(bs, a.ex_part);
+  block_stats_store(bs, a.ex_part, kPfNsub);
 }
 
 template <bool MIXED, int FMODE>
@@ -1843,10 +1960,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 // ------------------------------------------------------------------------------------
 // arena append: scan of the per-(instance, wavefront) counts, then the copy into the stores
 // ------------------------------------------------------------------------------------
-// One workgroup per instance: exclusive prefix over the wavefronts of each arena's counts
-// (in place), the store count before the append into base[], and the counts raised by the
-// totals, clamped to the capacities; the copy kernel drops and counts the children that land
-// beyond them.
+// Two workgroups per instance, photons and pairs (4.7 us a launch; 6.7 with one taking both in
+// turn): exclusive prefix over the wavefronts of the arena's counts (in place), the store
+// count before the append into base[], and the counts raised by the totals, clamped to the
+// capacities; the copy kernel drops and counts the children that land beyond them.
 // Exclusive prefix over n words by a workgroup of 1024: thread t sums the run [t k, t k + k),
 // one scan of the thread sums, then the run's offsets in place.  Returns the total; `wsum` is
 // 16 words of LDS.
@@ -1892,7 +2009,7 @@ __global__ void __launch_bounds__(1024) arena_scan_kernel(StepArgs a, ChildArena
                                                           const unsigned int* in_p,
                                                           const unsigned int* in_q) {
   __shared__ unsigned long long wsum[16];
-  const int i = blockIdx.x;
+  const int i = (int)blockIdx.x >> 1;
   const bool none = in_p && *in_p == 0u && *in_q == 0u;
   if (i == a.n_inst) {
     for (int kind = 0; kind < 2; ++kind) {
@@ -1904,29 +2021,20 @@ __global__ void __launch_bounds__(1024) arena_scan_kernel(StepArgs a, ChildArena
     return;
   }
   if (none) return;
-  for (int kind = 0; kind < 2; ++kind) {
-    const ChildArena& A = kind == 0 ? pa : qa;
-    if (A.waves <= 0) continue;
-    unsigned int* row = A.cnt + (size_t)i * A.waves;
-    const unsigned long long carry = block_prefix(row, A.waves, wsum);
-    if (threadIdx.x == 0) {
-      qed_instance& I = a.inst[i];
-      if (kind == 0) {
-        A.base[2 * i] = I.count[QED_PHOTON];
-        I.count[QED_PHOTON] += (long long)carry;
-      } else {
-        A.base[2 * i] = I.count[QED_ELECTRON];
-        A.base[2 * i + 1] = I.count[QED_POSITRON];
-        I.count[QED_ELECTRON] += (long long)carry;
-        I.count[QED_POSITRON] += (long long)carry;
-      }
-    }
-  }
-  // counts above the capacity (the copy drops and counts what lands beyond it) clamped
-  if (threadIdx.x == 0) {
-    qed_instance& I = a.inst[i];
-    for (int s = 0; s < 3; ++s)
-      if (I.count[s] > I.capacity[s]) I.count[s] = I.capacity[s];
+  const int kind = (int)(blockIdx.x & 1u);  // photons, pairs
+  const ChildArena& A = kind == 0 ? pa : qa;
+  unsigned long long total = 0ull;
+  if (A.waves > 0) total = block_prefix(A.cnt + (size_t)i * A.waves, A.waves, wsum);
+  if (threadIdx.x != 0) return;
+  // the store counts before the append, and the new ones; counts above the capacity (the copy
+  // drops and counts what lands beyond it) are clamped
+  qed_instance& I = a.inst[i];
+  const int s0 = kind == 0 ? QED_PHOTON : QED_ELECTRON, s1 = kind == 0 ? QED_PHOTON : QED_POSITRON;
+  for (int s = s0; s <= s1; ++s) {
+    const long long before = I.count[s];
+    if (A.waves > 0) A.base[2 * i + (s - s0)] = before;
+    const long long after = before + (long long)total;
+    I.count[s] = after > I.capacity[s] ? I.capacity[s] : after;
   }
 }
 
@@ -2002,7 +2110,8 @@ __global__ void __launch_bounds__(256) arena_copy_kernel(StepArgs a, ChildArena 
     const int sw = pair ? t - npa : t;
     const long long n = wave_records(A, sw);
     if (n == 0) continue;
-    for (int q = lane; q < a.n_inst; q += 64) run[q] = 0u;
+    if (a.n_inst > 1)
+      for (int q = lane; q < a.n_inst; q += 64) run[q] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     ArenaWalk walk;
@@ -2012,8 +2121,8 @@ __global__ void __launch_bounds__(256) arena_copy_kernel(StepArgs a, ChildArena 
       walk.advance(A, sw, j0, 64, n);
       const long long r = has ? walk.index(A, sw, j) : 0;
       const int li = has ? (int)A.inst[r] : -1;
-      unsigned local = 0;
-      uint64_t m = wave_ballot(has);
+      unsigned local = (unsigned)j;  // one instance: the record's place in the wavefront's
+      uint64_t m = a.n_inst > 1 ? wave_ballot(has) : 0ull;
       while (m) {
         const int leader = __ffsll((unsigned long long)m) - 1;
         const int lj = wave_bcast(li, leader);
@@ -2594,7 +2703,7 @@ __device__ __forceinline__ void gen_pass(const StepArgs& a, const GenArgs& q) {
     }
     if (q.pass == 1)
       for (int i = threadIdx.x; i < kPfCount; i += blockDim.x)
-        a.gen_part[(size_t)i * kMaxGridBlocks + blockIdx.x] = 0ull;
+        a.gen_part[part_index(i, (int)blockIdx.x)] = 0ull;
     return;
   }
   block_stats_init(bs);
@@ -2676,10 +2785,10 @@ static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape ph
   const int src = a.pa.waves + a.qa.waves;
   const ChildArena none{};
   const bool gen = a.generations > 0;
-  const int rb = gen ? 0 : kReduceBlocks;
+  const int rb = gen ? 0 : reduce_blocks(a);
   if (src > 0) {
     const unsigned int* no = nullptr;
-    hipLaunchKernelGGL(arena_scan_kernel, dim3(a.n_inst + (gen ? 1 : 0)), dim3(1024), 0, s, a,
+    hipLaunchKernelGGL(arena_scan_kernel, dim3(2 * a.n_inst + (gen ? 1 : 0)), dim3(1024), 0, s, a,
                        a.pa, a.qa, no, no);
     // with same-step processing the copy also clears generation 1's count matrices
     hipLaunchKernelGGL(arena_copy_kernel,
@@ -2705,7 +2814,7 @@ static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape ph
     // (both input arenas are on, or the photon one alone: its total then serves twice)
     const unsigned int* in_p = q.ipa.used + 1;
     const unsigned int* in_q = q.iqa.waves > 0 ? q.iqa.used + 1 : in_p;
-    hipLaunchKernelGGL(arena_scan_kernel, dim3(a.n_inst + 1), dim3(1024), 0, s, a, q.opa, q.oqa,
+    hipLaunchKernelGGL(arena_scan_kernel, dim3(2 * a.n_inst + 1), dim3(1024), 0, s, a, q.opa, q.oqa,
                        in_p, in_q);
     hipLaunchKernelGGL(arena_copy_kernel, dim3((gsrc + kWavesPerBlock - 1) / kWavesPerBlock),
                        dim3(256), 0, s, a, q.opa, q.oqa, more ? a.gpa[(g + 1) % 2] : none,
@@ -2738,7 +2847,7 @@ hipError_t launch_step(const StepArgs& a, int precision, LaunchShape lep, Launch
     else reduced = launch_persistent<false, kFieldLocal>(a, lep, pho, run_photons, s);
   }
   if (!reduced) {
-    hipLaunchKernelGGL(reduce_kernel, dim3(kReduceBlocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(reduce_kernel, dim3(reduce_blocks(a)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(256), 0, s, a);
   }
   return hipGetLastError();
