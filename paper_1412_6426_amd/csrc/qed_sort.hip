@@ -17,6 +17,15 @@
 // sort is a stable LSD radix sort over each instance's live slots (ties keep their order),
 // so the result is deterministic.
 //
+// The columns travel as records: the key pass, which reads the position anyway, packs each
+// slot's columns into one 80-byte record of the workspace, and the last pass reads the records
+// in sorted order and writes the columns back.  A particle that is not near its place costs one
+// or two lines of its record then, where a gather of eleven columns cost eleven.  The key pass,
+// the gather and the copy back took 85 us together on the grid cascade's lepton stores (up to
+// 1.7 10^6 slots each, nearly sorted), the key and the last pass now take 57; on 4 10^6 photons
+// in random order the gather alone took 843 us, and the two passes over the records that stand
+// for it in the thinning below take 112 and 196.
+//
 // Every kernel but the scans works tile by tile (kSortTile slots of one instance, one
 // workgroup each), so a tile's instance and slot base are found once; each thread loads
 // all of its items of a round before it stores any, which keeps many loads in flight.
@@ -25,12 +34,11 @@
 // sequence can be captured):
 //   sort_prep     one workgroup: live counts (none for a frozen instance), slot prefix and
 //                 tile prefix per instance;
-//   sort_key      keys and the identity permutation;
+//   sort_key      keys, the identity permutation, and the records;
 //   per pass:  sort_hist (digit counts per tile), scan_chunks, scan_sums, scan_apply
 //              (exclusive scan of the counts, ordered instance, digit, tile), sort_scatter
 //              (stable ranks within the tile);
-//   sort_gather   the columns, in sorted order, into the workspace;
-//   sort_store    the workspace back into the segments.
+//   sort_unpack   the records, in sorted order, into the columns.
 #include "qed_internal.h"
 
 namespace qedk {
@@ -52,9 +60,17 @@ struct SortArgs {
   unsigned* val[2];
   unsigned* cnt;     // [256 tiles]
   unsigned* sums;    // [chunks]
-  unsigned char* cols;
-  long long cap;     // slots (row length of the column copy)
+  struct Record* rec;  // [slots]
 };
+
+// One particle's columns.  A record is as many bytes as the columns hold, so that the copy
+// fits where a copy of the columns would.
+struct alignas(16) Record {
+  double x, y, z, px, py, pz, w;
+  unsigned long long id, parent;
+  unsigned birth, nev;
+};
+static_assert(sizeof(Record) == 80, "a record is read and written as five 16-byte words");
 
 constexpr int kSortThreads = 256;
 constexpr int kPerThread = kSortTile / kSortThreads;  // items of one thread in a tile
@@ -119,18 +135,17 @@ __global__ void __launch_bounds__(kSortThreads) sort_key_kernel(SortArgs a) {
   Tile T;
   if (!tile_of(a, blockIdx.x, T)) return;
   const bool photons = a.species == QED_PHOTON;
+  const qed_soa& S = a.s;
+  const bool nev = S.n_events != nullptr;
   for (long long r0 = T.g0 + threadIdx.x; r0 < T.g1; r0 += kBatch * kSortThreads) {
-    double x[kBatch], y[kBatch], z[kBatch];
-    uint64_t id[kBatch];
+    Record q[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const long long g = r0 + (long long)u * kSortThreads;
       if (g < T.g1) {
         const long long s = T.sbase + g;
-        id[u] = photons ? a.s.id[s] : 0ull;
-        x[u] = a.s.x[s];
-        y[u] = a.s.y[s];
-        z[u] = a.s.z[s];
+        q[u] = {S.x[s], S.y[s], S.z[s], S.px[s], S.py[s], S.pz[s], S.w[s],
+                S.id[s], S.parent[s], S.birth[s], nev ? S.n_events[s] : 0u};
       }
     }
 #pragma unroll
@@ -138,15 +153,16 @@ __global__ void __launch_bounds__(kSortThreads) sort_key_kernel(SortArgs a) {
       const long long g = r0 + (long long)u * kSortThreads;
       if (g >= T.g1) break;
       unsigned key = a.dead;
-      if (!photons || id[u] != QED_ID_DEAD) {
-        const long long bx = axis_block(x[u], a.origin[0], a.dx[0], a.n[0], a.shift);
-        const long long by = axis_block(y[u], a.origin[1], a.dx[1], a.n[1], a.shift);
-        const long long bz = axis_block(z[u], a.origin[2], a.dx[2], a.n[2], a.shift);
+      if (!photons || q[u].id != QED_ID_DEAD) {
+        const long long bx = axis_block(q[u].x, a.origin[0], a.dx[0], a.n[0], a.shift);
+        const long long by = axis_block(q[u].y, a.origin[1], a.dx[1], a.n[1], a.shift);
+        const long long bz = axis_block(q[u].z, a.origin[2], a.dx[2], a.n[2], a.shift);
         if (bx < 0 || by < 0 || bz < 0) key = a.dead - 1u;  // last of the live particles
         else key = (unsigned)((bz * a.nb[1] + by) * a.nb[0] + bx);
       }
       a.key[0][g] = key;
       a.val[0][g] = (unsigned)g;
+      a.rec[g] = q[u];
     }
   }
 }
@@ -326,138 +342,65 @@ __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(SortArgs a, 
   }
 }
 
-// Column copy in the workspace: 7 doubles, id and parent, birth and n_events per slot.
-struct ColView {
-  double* d[7];
-  unsigned long long *id, *parent;
-  unsigned *birth, *nev;
-};
-__device__ __forceinline__ ColView col_view(const SortArgs& a) {
-  ColView c;
-  const size_t col8 = ((size_t)a.cap * 8 + 255) & ~(size_t)255;
-  const size_t col4 = ((size_t)a.cap * 4 + 255) & ~(size_t)255;
-  unsigned char* p = a.cols;
-  for (int k = 0; k < 7; ++k) {
-    c.d[k] = reinterpret_cast<double*>(p);
-    p += col8;
-  }
-  c.id = reinterpret_cast<unsigned long long*>(p);
-  p += col8;
-  c.parent = reinterpret_cast<unsigned long long*>(p);
-  p += col8;
-  c.birth = reinterpret_cast<unsigned*>(p);
-  p += col4;
-  c.nev = reinterpret_cast<unsigned*>(p);
-  return c;
+__device__ __forceinline__ void write_slot(const qed_soa& s, long long i, const Record& q) {
+  s.x[i] = q.x;
+  s.y[i] = q.y;
+  s.z[i] = q.z;
+  s.px[i] = q.px;
+  s.py[i] = q.py;
+  s.pz[i] = q.pz;
+  s.w[i] = q.w;
+  s.id[i] = q.id;
+  s.parent[i] = q.parent;
+  s.birth[i] = q.birth;
+  if (s.n_events) s.n_events[i] = q.nev;
 }
 
-// One particle's columns.
-struct Item {
-  double d[7];
-  unsigned long long id, parent;
-  unsigned birth, nev;
-};
-
-// Items of the tile in sorted order (through the permutation, which stays inside the
-// instance) into the workspace rows of the same index.
-__global__ void __launch_bounds__(kSortThreads) sort_gather_kernel(SortArgs a, int last) {
+// The tile's records in sorted order (through the permutation, which stays inside the
+// instance) into the columns.
+__global__ void __launch_bounds__(kSortThreads) sort_unpack_kernel(SortArgs a, int last) {
   Tile T;
   if (!tile_of(a, blockIdx.x, T)) return;
-  const ColView c = col_view(a);
   const unsigned* perm = a.val[last];
-  const qed_soa& s = a.s;
-  const bool nev = s.n_events != nullptr;
   for (long long r0 = T.g0 + threadIdx.x; r0 < T.g1; r0 += kBatch * kSortThreads) {
-    Item it[kBatch];
+    Record q[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const long long g = r0 + (long long)u * kSortThreads;
-      if (g < T.g1) {
-        const long long i = T.sbase + (long long)perm[g];
-        it[u].d[0] = s.x[i];
-        it[u].d[1] = s.y[i];
-        it[u].d[2] = s.z[i];
-        it[u].d[3] = s.px[i];
-        it[u].d[4] = s.py[i];
-        it[u].d[5] = s.pz[i];
-        it[u].d[6] = s.w[i];
-        it[u].id = s.id[i];
-        it[u].parent = s.parent[i];
-        it[u].birth = s.birth[i];
-        it[u].nev = nev ? s.n_events[i] : 0u;
-      }
+      if (g < T.g1) q[u] = a.rec[perm[g]];
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const long long g = r0 + (long long)u * kSortThreads;
-      if (g >= T.g1) break;
-      for (int k = 0; k < 7; ++k) c.d[k][g] = it[u].d[k];
-      c.id[g] = it[u].id;
-      c.parent[g] = it[u].parent;
-      c.birth[g] = it[u].birth;
-      c.nev[g] = it[u].nev;
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kSortThreads) sort_store_kernel(SortArgs a) {
-  Tile T;
-  if (!tile_of(a, blockIdx.x, T)) return;
-  const ColView c = col_view(a);
-  const qed_soa& s = a.s;
-  const bool nev = s.n_events != nullptr;
-  for (long long r0 = T.g0 + threadIdx.x; r0 < T.g1; r0 += kBatch * kSortThreads) {
-    Item it[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const long long g = r0 + (long long)u * kSortThreads;
-      if (g < T.g1) {
-        for (int k = 0; k < 7; ++k) it[u].d[k] = c.d[k][g];
-        it[u].id = c.id[g];
-        it[u].parent = c.parent[g];
-        it[u].birth = c.birth[g];
-        it[u].nev = c.nev[g];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const long long g = r0 + (long long)u * kSortThreads;
-      if (g >= T.g1) break;
-      const long long i = T.sbase + g;
-      s.x[i] = it[u].d[0];
-      s.y[i] = it[u].d[1];
-      s.z[i] = it[u].d[2];
-      s.px[i] = it[u].d[3];
-      s.py[i] = it[u].d[4];
-      s.pz[i] = it[u].d[5];
-      s.w[i] = it[u].d[6];
-      s.id[i] = it[u].id;
-      s.parent[i] = it[u].parent;
-      s.birth[i] = it[u].birth;
-      if (nev) s.n_events[i] = it[u].nev;
+      if (g < T.g1) write_slot(a.s, T.sbase + g, q[u]);
     }
   }
 }
 
 // ------------------------------------------------------------------------------------
-// Thinning per cell (qed_thin_cells), on the store the sort above has just ordered: a
-// group is a run of one key within an instance.  Heads (first items of groups) are counted
-// per tile and scanned, which numbers the groups; one thread per group then sums its weight,
-// draws its survivors and fixes its factor, in store order, as a sequential loop does; the
-// survivors are ranked per tile, scanned, gathered with their new weights into the column
-// copy and written back to the segments, whose counts and records the last launch sets.
+// Thinning per cell (qed_thin_cells), on the records in the order of the sort above: a
+// group is a run of one key within an instance.  The weights and ids alone are written in
+// sorted order first (into the store's columns, which the records have replaced).  Heads
+// (first items of groups) are counted per tile and scanned, which numbers the groups; each
+// group's weight, survivors and factor follow in store order, as a sequential loop takes them,
+// by a thread in small groups and a wavefront in larger ones; the survivors are ranked per
+// tile, scanned, and their records written with their new weights to the segments, whose
+// counts and records the last launches set.
 // ------------------------------------------------------------------------------------
+constexpr int kPartWords = 6;
 struct ThinArgs {
   const unsigned* key;  // sorted keys
+  const unsigned* perm; // the record of each item (the sort's last index array)
   unsigned* gid;        // group of each item
-  unsigned* keep;       // survival flag of each item
+  unsigned char* keep;  // survival flag of each item
   unsigned* kpre;       // survivor rank of each item within its tile
   unsigned* hcnt;       // per tile: heads, then (scanned) heads before the tile
   unsigned* kcnt;       // per tile: survivors, then (scanned) survivors before the tile
   unsigned* gstart;     // [groups + 1] first item of each group
   double *gfac, *gw, *gwa;
   unsigned* gkept;
-  unsigned* big;        // groups of more than kBigGroup particles, for thin_big_kernel
+  unsigned* big;        // groups of more than kSmallGroup particles, for the two kernels below
+  double* part;         // [n_inst][finish_parts][kPartWords] partial sums of the records
   long long* gpfx;      // [n_inst + 1] groups before each instance
   long long* kpref;     // [n_inst + 1] survivors before each instance
   long long max_per_cell;
@@ -489,6 +432,26 @@ __global__ void __launch_bounds__(kSortThreads) thin_heads_kernel(SortArgs a, Th
   __shared__ unsigned sw[4];
   Tile T;
   if (!tile_of(a, blockIdx.x, T)) return;
+  for (long long r0 = T.g0 + threadIdx.x; r0 < T.g1; r0 += kBatch * kSortThreads) {
+    double w[kBatch];
+    unsigned long long id[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const long long g = r0 + (long long)u * kSortThreads;
+      if (g < T.g1) {
+        const Record& q = a.rec[t.perm[g]];
+        w[u] = q.w;
+        id[u] = q.id;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const long long g = r0 + (long long)u * kSortThreads;
+      if (g >= T.g1) break;
+      a.s.w[T.sbase + g] = w[u];
+      a.s.id[T.sbase + g] = id[u];
+    }
+  }
   unsigned f[kPerThread], pre[kPerThread];
 #pragma unroll
   for (int i = 0; i < kPerThread; ++i) {
@@ -554,8 +517,11 @@ __global__ void __launch_bounds__(kSortThreads) thin_groups_kernel(SortArgs a, T
   }
 }
 
-// Groups of more particles than this go to thin_big_kernel (a workgroup each); smaller ones
-// are walked by one thread, in store order.
+// A group of up to kSmallGroup particles is walked by one thread, one of up to kBigGroup by a
+// wavefront, whose lanes hold 64 particles and add them up in store order, and a larger one by
+// a workgroup in another fixed order.  (A thread took the longest group's 900 particles one
+// load after the other: 356 us for 4 10^6 photons against 18 and 69.)
+constexpr long long kSmallGroup = 24;
 constexpr long long kBigGroup = 1024;
 
 // The survival draw of one particle.
@@ -565,37 +531,46 @@ __device__ __forceinline__ double thin_draw(uint64_t id, uint64_t seed, uint32_t
 }
 
 // One thread per group, in store order within the group: its weight, its survivors and its
-// factor (a group of removed photons: none, factor 0).  Groups of more than kBigGroup
-// particles are listed for thin_big_kernel.
+// factor (a group of removed photons: none, factor 0).  Larger groups are listed.
 __global__ void __launch_bounds__(kSortThreads) thin_decide_kernel(SortArgs a, ThinArgs t) {
   const long long groups = a.hdr->groups;
   const long long M = t.max_per_cell;
   const uint32_t step = (uint32_t)*t.d_step;
   const qed_soa& S = a.s;
   const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < groups; q += stride) {
-    const long long g0 = t.gstart[q], g1 = t.gstart[q + 1];
-    const int inst = find_instance(a.gpref, a.n_inst, g0);
-    const long long sb = a.inst[inst].base[a.species] - a.gpref[inst];
+  for (long long q0 = (long long)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); q0 < groups;
+       q0 += stride) {
+    const long long q = q0 + lane_id();
+    const bool has = q < groups;
+    const long long g0 = has ? t.gstart[q] : 0, g1 = has ? t.gstart[q + 1] : 0;
     const long long m = g1 - g0;
-    if (m > kBigGroup) {  // removed photons too: all their flags are cleared there
-      const unsigned long long at = atomicAdd(reinterpret_cast<unsigned long long*>(&a.hdr->nbig), 1ull);
-      t.big[at] = (unsigned)q;
-      continue;
+    // removed photons too: all their flags are cleared there
+    const bool listed = m > kSmallGroup;
+    const uint64_t lm = wave_ballot(listed);
+    if (lm) {  // one reservation per wavefront
+      long long at = 0;
+      if (lane_id() == 0)
+        at = (long long)atomicAdd(reinterpret_cast<unsigned long long*>(&a.hdr->nbig),
+                                  (unsigned long long)__popcll(lm));
+      at = wave_bcast(at, 0);
+      if (listed) t.big[at + __popcll(lm & lanes_below())] = (unsigned)q;
     }
+    if (!has || listed) continue;
     if (t.key[g0] == a.dead) {  // removed photons
-      for (long long g = g0; g < g1; ++g) t.keep[g] = 0u;
+      for (long long g = g0; g < g1; ++g) t.keep[g] = 0;
       t.gfac[q] = 0.0;
       t.gw[q] = 0.0;
       t.gwa[q] = 0.0;
       t.gkept[q] = 0u;
       continue;
     }
+    const int inst = find_instance(a.gpref, a.n_inst, g0);
+    const long long sb = a.inst[inst].base[a.species] - a.gpref[inst];
     double W = 0.0;
     for (long long g = g0; g < g1; ++g) W += S.w[sb + g];
     t.gw[q] = W;
     if (m <= M) {
-      for (long long g = g0; g < g1; ++g) t.keep[g] = 1u;
+      for (long long g = g0; g < g1; ++g) t.keep[g] = 1;
       t.gfac[q] = 1.0;
       t.gwa[q] = W;
       t.gkept[q] = (unsigned)m;
@@ -608,7 +583,7 @@ __global__ void __launch_bounds__(kSortThreads) thin_decide_kernel(SortArgs a, T
     for (long long g = g0; g < g1; ++g) {
       const double u = thin_draw(S.id[sb + g], seed, step);
       const bool k = u < qs;
-      t.keep[g] = k ? 1u : 0u;
+      t.keep[g] = k ? 1 : 0;
       if (k) {
         ++kept;
         K += S.w[sb + g];
@@ -619,7 +594,7 @@ __global__ void __launch_bounds__(kSortThreads) thin_decide_kernel(SortArgs a, T
       }
     }
     if (kept == 0) {  // the group keeps its weight in its smallest draw
-      t.keep[gmin] = 1u;
+      t.keep[gmin] = 1;
       K = S.w[sb + gmin];
       kept = 1;
     }
@@ -630,6 +605,120 @@ __global__ void __launch_bounds__(kSortThreads) thin_decide_kernel(SortArgs a, T
     t.gfac[q] = fac;
     t.gwa[q] = Wa;
     t.gkept[q] = (unsigned)kept;
+  }
+}
+
+// sum + the lanes' values in lane order, one after the other (wavefront-uniform result).
+__device__ __forceinline__ double add_in_order(double sum, double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+#pragma unroll
+  for (int l = 0; l < 64; ++l)
+    sum += __hiloint2double(__builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(lo, l));
+  return sum;
+}
+
+// One wavefront per listed group of at most kBigGroup particles: the same decisions and the
+// same sums in the same order as thin_decide_kernel (a particle that a sum leaves out adds 0,
+// which leaves a positive sum as it is).
+__global__ void __launch_bounds__(kSortThreads) thin_mid_kernel(SortArgs a, ThinArgs t) {
+  const long long nbig = a.hdr->nbig;
+  const long long M = t.max_per_cell;
+  const uint32_t step = (uint32_t)*t.d_step;
+  const qed_soa& S = a.s;
+  const int lane = lane_id();
+  const long long V = (long long)gridDim.x * (kSortThreads / 64);
+  constexpr int kRows = (int)(kBigGroup / 64);
+  for (long long b = (long long)blockIdx.x * (kSortThreads / 64) + (threadIdx.x >> 6); b < nbig;
+       b += V) {
+    const unsigned q = (unsigned)__builtin_amdgcn_readfirstlane((int)t.big[b]);
+    const long long g0 = t.gstart[q], g1 = t.gstart[q + 1];
+    const long long m = g1 - g0;
+    if (m > kBigGroup) continue;
+    if (t.key[g0] == a.dead) {  // removed photons
+      for (long long g = g0 + lane; g < g1; g += 64) t.keep[g] = 0;
+      if (lane == 0) {
+        t.gfac[q] = 0.0;
+        t.gw[q] = 0.0;
+        t.gwa[q] = 0.0;
+        t.gkept[q] = 0u;
+      }
+      continue;
+    }
+    const int inst = find_instance(a.gpref, a.n_inst, g0);
+    const long long sb = a.inst[inst].base[a.species] - a.gpref[inst];
+    double w[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const long long g = g0 + r * 64 + lane;
+      w[r] = g < g1 ? S.w[sb + g] : 0.0;
+    }
+    double W = 0.0;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+      if (r * 64 < m) W = add_in_order(W, w[r]);
+    if (m <= M) {
+      for (long long g = g0 + lane; g < g1; g += 64) t.keep[g] = 1;
+      if (lane == 0) {
+        t.gw[q] = W;
+        t.gfac[q] = 1.0;
+        t.gwa[q] = W;
+        t.gkept[q] = (unsigned)m;
+      }
+      continue;
+    }
+    const double qs = (double)M / (double)m;
+    const uint64_t seed = a.inst[inst].seed;
+    double K = 0.0, umin = 2.0;
+    long long kept = 0, gmin = g1;
+    unsigned rows = 0u;  // bit r: this lane's particle of row r survives
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      if (r * 64 < m) {
+        const long long g = g0 + r * 64 + lane;
+        bool k = false;
+        if (g < g1) {
+          const double u = thin_draw(S.id[sb + g], seed, step);
+          k = u < qs;
+          t.keep[g] = k ? 1 : 0;
+          if (u < umin) {
+            umin = u;
+            gmin = g;
+          }
+        }
+        rows |= k ? 1u << r : 0u;
+        kept += __popcll(wave_ballot(k));
+        K = add_in_order(K, k ? w[r] : 0.0);
+      }
+    }
+    if (kept == 0) {  // the group keeps its weight in its smallest draw (the first on a tie)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double u = __shfl_xor(umin, o, 64);
+        const long long g = __shfl_xor(gmin, o, 64);
+        if (u < umin || (u == umin && g < gmin)) {
+          umin = u;
+          gmin = g;
+        }
+      }
+      const bool own = (int)((gmin - g0) & 63) == lane;
+      rows = own ? 1u << (int)((gmin - g0) >> 6) : 0u;
+      if (own) t.keep[gmin] = 1;
+      K = S.w[sb + gmin];
+      kept = 1;
+    }
+    const double fac = W / K;
+    double Wa = 0.0;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const double p = w[r] * fac;
+      if (r * 64 < m) Wa = add_in_order(Wa, (rows >> r) & 1u ? p : 0.0);
+    }
+    if (lane == 0) {
+      t.gw[q] = W;
+      t.gfac[q] = fac;
+      t.gwa[q] = Wa;
+      t.gkept[q] = (unsigned)kept;
+    }
   }
 }
 
@@ -663,9 +752,10 @@ __global__ void __launch_bounds__(kSortThreads) thin_big_kernel(SortArgs a, Thin
   for (long long b = blockIdx.x; b < nbig; b += gridDim.x) {
     const long long q = t.big[b];
     const long long g0 = t.gstart[q], g1 = t.gstart[q + 1];
+    const long long m = g1 - g0;
+    if (m <= kBigGroup) continue;  // thin_mid_kernel's
     const int inst = find_instance(a.gpref, a.n_inst, g0);
     const long long sb = a.inst[inst].base[a.species] - a.gpref[inst];
-    const long long m = g1 - g0;
     if (t.key[g0] == a.dead) {  // removed photons
       for (long long g = g0 + tid; g < g1; g += kSortThreads) t.keep[g] = 0u;
       if (tid == 0) {
@@ -769,77 +859,50 @@ __global__ void __launch_bounds__(kSortThreads) thin_keep_kernel(SortArgs a, Thi
   if (threadIdx.x == 0) t.kcnt[blockIdx.x] = total;
 }
 
-// Survivors of the tile into the column copy at their rank among all survivors, with the
-// group's factor on the weight.
-__global__ void __launch_bounds__(kSortThreads) thin_gather_kernel(SortArgs a, ThinArgs t) {
+// Survivors of the tile into the segment at their rank among the instance's survivors, with
+// the group's factor on the weight.
+__global__ void __launch_bounds__(kSortThreads) thin_store_kernel(SortArgs a, ThinArgs t) {
   Tile T;
   if (!tile_of(a, blockIdx.x, T)) return;
-  const ColView c = col_view(a);
-  const qed_soa& s = a.s;
-  const bool nev = s.n_events != nullptr;
-  const long long base = (long long)t.kcnt[blockIdx.x];
-  for (long long g = T.g0 + threadIdx.x; g < T.g1; g += kSortThreads) {
-    if (!t.keep[g]) continue;
-    const long long i = T.sbase + g;
-    const long long d = base + (long long)t.kpre[g];
-    c.d[0][d] = s.x[i];
-    c.d[1][d] = s.y[i];
-    c.d[2][d] = s.z[i];
-    c.d[3][d] = s.px[i];
-    c.d[4][d] = s.py[i];
-    c.d[5][d] = s.pz[i];
-    c.d[6][d] = s.w[i] * t.gfac[t.gid[g]];
-    c.id[d] = s.id[i];
-    c.parent[d] = s.parent[i];
-    c.birth[d] = s.birth[i];
-    c.nev[d] = nev ? s.n_events[i] : 0u;
+  const long long to = a.inst[T.inst].base[a.species] + (long long)t.kcnt[blockIdx.x] -
+                       t.kpref[T.inst];
+  for (long long r0 = T.g0 + threadIdx.x; r0 < T.g1; r0 += kBatch * kSortThreads) {
+    Record q[kBatch];
+    long long d[kBatch];
+    bool k[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const long long g = r0 + (long long)u * kSortThreads;
+      k[u] = g < T.g1 && t.keep[g];
+      if (k[u]) {
+        q[u] = a.rec[t.perm[g]];
+        q[u].w *= t.gfac[t.gid[g]];
+        d[u] = to + (long long)t.kpre[g];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (k[u]) write_slot(a.s, d[u], q[u]);
   }
 }
 
-// The column copy back into the segments: survivor j of instance i goes to slot
-// base_i + (j - survivors before instance i).
-__global__ void __launch_bounds__(kSortThreads) thin_store_kernel(SortArgs a, ThinArgs t) {
-  const long long kept = a.hdr->kept;
-  const ColView c = col_view(a);
-  const qed_soa& s = a.s;
-  const bool nev = s.n_events != nullptr;
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x; j < kept; j += stride) {
-    const int inst = find_instance(t.kpref, a.n_inst, j);
-    const long long i = a.inst[inst].base[a.species] + (j - t.kpref[inst]);
-    const double x = c.d[0][j], y = c.d[1][j], z = c.d[2][j];
-    const double px = c.d[3][j], py = c.d[4][j], pz = c.d[5][j], w = c.d[6][j];
-    const unsigned long long id = c.id[j], parent = c.parent[j];
-    const unsigned birth = c.birth[j], ne = c.nev[j];
-    s.x[i] = x;
-    s.y[i] = y;
-    s.z[i] = z;
-    s.px[i] = px;
-    s.py[i] = py;
-    s.pz[i] = pz;
-    s.w[i] = w;
-    s.id[i] = id;
-    s.parent[i] = parent;
-    s.birth[i] = birth;
-    if (nev) s.n_events[i] = ne;
-  }
+// Workgroups that share the sums over one instance's groups.
+__host__ __device__ inline int finish_parts(long long slots, int n_inst) {
+  const long long p = slots / (4096ll * n_inst);
+  return p < 1 ? 1 : p > 256 ? 256 : (int)p;
 }
 
-// One workgroup per instance: the new count and the record (fixed-order reductions over
-// the instance's groups).
-__global__ void __launch_bounds__(kSortThreads) thin_finish_kernel(SortArgs a, ThinArgs t) {
+// Sums over the groups of instance blockIdx.y, part blockIdx.x of them (fixed-order
+// reductions): one workgroup over a grid's groups took 390 us for 3 10^5 of them.
+__global__ void __launch_bounds__(kSortThreads) thin_sums_kernel(SortArgs a, ThinArgs t) {
   __shared__ double sd[2][kSortThreads];
   __shared__ long long sl[3][kSortThreads];
-  const int i = blockIdx.x;
-  qed_instance& I = a.inst[i];
-  qed_thin_cells_record* r = t.rec + i;
-  if (I.frozen) {
-    if (threadIdx.x == 0) *r = qed_thin_cells_record{};
-    return;
-  }
+  const int i = blockIdx.y, P = (int)gridDim.x;
+  const long long q0 = t.gpfx[i], q1 = t.gpfx[i + 1], len = (q1 - q0 + P - 1) / P;
+  const long long lo = q0 + (long long)blockIdx.x * len, hi = lo + len < q1 ? lo + len : q1;
   double wb = 0.0, wa = 0.0;
   long long live = 0, groups = 0, thinned = 0;
-  for (long long q = t.gpfx[i] + threadIdx.x; q < t.gpfx[i + 1]; q += blockDim.x) {
+  for (long long q = lo + threadIdx.x; q < hi; q += blockDim.x) {
     const long long g0 = t.gstart[q], m = (long long)t.gstart[q + 1] - g0;
     if (t.key[g0] == a.dead) continue;
     live += m;
@@ -863,15 +926,38 @@ __global__ void __launch_bounds__(kSortThreads) thin_finish_kernel(SortArgs a, T
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const long long kept = t.kpref[i + 1] - t.kpref[i];
-    I.count[a.species] = kept;
-    r->live_before = sl[0][0];
-    r->kept = kept;
-    r->groups = sl[1][0];
-    r->groups_thinned = sl[2][0];
-    r->weight_before = sd[0][0];
-    r->weight_after = sd[1][0];
+    double* p = t.part + kPartWords * ((size_t)i * P + blockIdx.x);
+    p[0] = sd[0][0];
+    p[1] = sd[1][0];
+    for (int k = 0; k < 3; ++k) p[2 + k] = (double)sl[k][0];  // below 2^32
   }
+}
+
+// One wavefront per instance: the new count and the record (lane l takes parts l, l + 64, ..;
+// then a fixed tree).
+__global__ void __launch_bounds__(kSortThreads) thin_finish_kernel(SortArgs a, ThinArgs t,
+                                                                   int parts) {
+  const int i = (int)blockIdx.x * (kSortThreads / 64) + (int)(threadIdx.x >> 6);
+  if (i >= a.n_inst) return;
+  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int p = lane_id(); p < parts; p += 64)
+    for (int k = 0; k < 5; ++k) v[k] += t.part[kPartWords * ((size_t)i * parts + p) + k];
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+  if (lane_id() != 0) return;
+  qed_instance& I = a.inst[i];
+  qed_thin_cells_record r{};
+  if (!I.frozen) {
+    r.weight_before = v[0];
+    r.weight_after = v[1];
+    r.live_before = (long long)v[2];
+    r.groups = (long long)v[3];
+    r.groups_thinned = (long long)v[4];
+    r.kept = t.kpref[i + 1] - t.kpref[i];
+    I.count[a.species] = r.kept;
+  }
+  t.rec[i] = r;
 }
 
 }  // namespace
@@ -922,13 +1008,13 @@ SortArgs sort_args(const qed_soa& s, int species, qed_instance* inst, int n_inst
   }
   a.cnt = reinterpret_cast<unsigned*>(w + L.cnt);
   a.sums = reinterpret_cast<unsigned*>(w + L.sums);
-  a.cols = w + L.cols;
-  a.cap = L.cap;
+  a.rec = reinterpret_cast<Record*>(w + L.cols);
   return a;
 }
 
-void enqueue_sort(const SortArgs& a, const SortLayout& L, const SortGeometry& geo,
-                  hipStream_t st) {
+// The records and the sorted permutation of them.
+void enqueue_order(const SortArgs& a, const SortLayout& L, const SortGeometry& geo,
+                   hipStream_t st) {
   const unsigned grid = (unsigned)L.tiles_max;  // one workgroup per possible tile
   const unsigned chunks = (unsigned)((L.tiles_max * 256 + kScanChunk - 1) / kScanChunk);
   const dim3 blk(kSortThreads);
@@ -941,8 +1027,6 @@ void enqueue_sort(const SortArgs& a, const SortLayout& L, const SortGeometry& ge
     hipLaunchKernelGGL(scan_apply_kernel, dim3(chunks), blk, 0, st, a);
     hipLaunchKernelGGL(sort_scatter_kernel, dim3(grid), blk, 0, st, a, pass);
   }
-  hipLaunchKernelGGL(sort_gather_kernel, dim3(grid), blk, 0, st, a, geo.passes & 1);
-  hipLaunchKernelGGL(sort_store_kernel, dim3(grid), blk, 0, st, a);
 }
 
 }  // namespace
@@ -954,7 +1038,9 @@ hipError_t launch_sort_cells(const qed_soa& s, int species, qed_instance* inst, 
   const SortGeometry geo = sort_geometry(n);
   const SortArgs a = sort_args(s, species, inst, n_inst, L, geo, n, dx, origin,
                                static_cast<unsigned char*>(work));
-  enqueue_sort(a, L, geo, st);
+  enqueue_order(a, L, geo, st);
+  hipLaunchKernelGGL(sort_unpack_kernel, dim3((unsigned)L.tiles_max), dim3(kSortThreads), 0, st,
+                     a, geo.passes & 1);
   return hipGetLastError();
 }
 
@@ -967,11 +1053,14 @@ hipError_t launch_thin_cells(const qed_soa& s, int species, qed_instance* inst, 
   const SortGeometry geo = sort_geometry(n);
   unsigned char* w = static_cast<unsigned char*>(work);
   const SortArgs a = sort_args(s, species, inst, n_inst, L.sort, geo, n, dx, origin, w);
-  enqueue_sort(a, L.sort, geo, st);
+  enqueue_order(a, L.sort, geo, st);
+  // The sort's other key and index arrays take each item's group and survivor rank, and the
+  // second half of the list of large groups the survival flags: a listed group holds more than
+  // kSmallGroup particles, so the list fills a small part of its array.
   ThinArgs t{};
   t.key = a.key[geo.passes & 1];
   t.gid = a.key[(geo.passes + 1) & 1];
-  t.keep = a.val[geo.passes & 1];
+  t.perm = a.val[geo.passes & 1];
   t.kpre = a.val[(geo.passes + 1) & 1];
   t.hcnt = a.cnt;
   t.kcnt = a.cnt + L.sort.tiles_max;
@@ -981,6 +1070,12 @@ hipError_t launch_thin_cells(const qed_soa& s, int species, qed_instance* inst, 
   t.gwa = reinterpret_cast<double*>(w + L.gwa);
   t.gkept = reinterpret_cast<unsigned*>(w + L.gkept);
   t.big = reinterpret_cast<unsigned*>(w + L.big);
+  t.keep = w + L.big + (((size_t)L.sort.cap + 1) / 2) * sizeof(unsigned);
+  // partial sums: several parts an instance (each of 4096 slots or more) where the factors
+  // were, which thin_store_kernel reads last; one part an instance in its record
+  const int parts = finish_parts(slots, n_inst);
+  static_assert(sizeof(qed_thin_cells_record) == kPartWords * sizeof(double), "a part fits");
+  t.part = parts > 1 ? reinterpret_cast<double*>(w + L.gfac) : reinterpret_cast<double*>(rec);
   t.gpfx = reinterpret_cast<long long*>(w + L.gpfx);
   t.kpref = reinterpret_cast<long long*>(w + L.kpref);
   t.max_per_cell = max_per_cell;
@@ -994,12 +1089,14 @@ hipError_t launch_thin_cells(const qed_soa& s, int species, qed_instance* inst, 
   hipLaunchKernelGGL(thin_scan_kernel, dim3(1), blk, 0, st, a, t, 0);
   hipLaunchKernelGGL(thin_groups_kernel, dim3(grid), blk, 0, st, a, t);
   hipLaunchKernelGGL(thin_decide_kernel, dim3(group_blocks), blk, 0, st, a, t);
+  hipLaunchKernelGGL(thin_mid_kernel, dim3(1024), blk, 0, st, a, t);
   hipLaunchKernelGGL(thin_big_kernel, dim3(1024), blk, 0, st, a, t);
   hipLaunchKernelGGL(thin_keep_kernel, dim3(grid), blk, 0, st, a, t);
   hipLaunchKernelGGL(thin_scan_kernel, dim3(1), blk, 0, st, a, t, 1);
-  hipLaunchKernelGGL(thin_gather_kernel, dim3(grid), blk, 0, st, a, t);
-  hipLaunchKernelGGL(thin_store_kernel, dim3(group_blocks), blk, 0, st, a, t);
-  hipLaunchKernelGGL(thin_finish_kernel, dim3((unsigned)n_inst), blk, 0, st, a, t);
+  hipLaunchKernelGGL(thin_store_kernel, dim3(grid), blk, 0, st, a, t);
+  hipLaunchKernelGGL(thin_sums_kernel, dim3((unsigned)parts, (unsigned)n_inst), blk, 0, st, a, t);
+  hipLaunchKernelGGL(thin_finish_kernel, dim3((unsigned)((n_inst + 3) / 4)), blk, 0, st, a, t,
+                     parts);
   return hipGetLastError();
 }
 
