@@ -88,6 +88,18 @@ __global__ void __launch_bounds__(256) w_panel_kernel(TrialArgs a) {
   a.part[k] = gauss_legendre(a, mt, ser, edge(a, k), edge(a, k + 1));
 }
 
+// W's integrand at the start of every interval, over the interval's own integral (both are
+// needed once, in turn).
+__global__ void __launch_bounds__(256) w_edge_kernel(TrialArgs a) {
+  __shared__ MathTab mt;
+  stage_math(mt);
+  __syncthreads();
+  const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= a.panels) return;
+  const Series64 ser = series_of(a.tables);
+  a.part[k] = integrand(a, mt, ser, edge(a, k));
+}
+
 // cum[0] = 0, cum[k + 1] = cum[k] + part[k]: each thread sums one contiguous run, the run
 // totals are scanned in LDS, then each run is written out (a fixed order of additions).
 __global__ void __launch_bounds__(kScanThreads) w_scan_kernel(TrialArgs a) {
@@ -132,22 +144,38 @@ __device__ double standard_delta(const TrialArgs& a, const MathTab& mt, const Se
   const double base = cum[lo], span = cum[lo + 1] - base;
   const double want = target - base;
   double blo = ua, bhi = ub;
-  double u = span > 0.0 ? ua + (ub - ua) * (want / span) : 0.5 * (ua + ub);
+  // Start: the root of the cubic through W and its slope at the interval's ends, which differs
+  // from W by 1e-10 of the interval or less, so that one Newton step on the quadrature mostly
+  // ends it (from the chord it took two or three, each nine evaluations of the rate).
+  const double h = ub - ua;
+  double u = 0.5 * (ua + ub);
+  if (span > 0.0) {
+    const double fa = h * a.part[lo], fb = lo + 1 < a.panels ? h * a.part[lo + 1] : 0.0;
+    const double c2 = 3.0 * span - 2.0 * fa - fb, c3 = fa + fb - 2.0 * span;
+    double t = want / span;
+#pragma unroll
+    for (int it = 0; it < 3; ++it) {
+      const double g = fma(t, fma(t, fma(t, c3, c2), fa), -want);
+      const double f = fma(t, fma(t, 3.0 * c3, 2.0 * c2), fa);
+      t -= f > 0.0 ? g / f : 0.0;
+    }
+    u = ua + h * t;
+  }
   if (!(u > blo && u < bhi)) u = 0.5 * (blo + bhi);
   const double tol = 0x1p-50 * fmax(fmax(fabs(ua), fabs(ub)), 1.0);
+  // a Newton step d leaves an error of |f'/f| d^2 / 2, and the integrand's logarithmic slope in
+  // u stays below 128: steps below this end the iteration
+  const double last = 0.125 * sqrt(tol);
   for (int it = 0; it < 60; ++it) {
     const double g = gauss_legendre(a, mt, ser, ua, u) - want;
     if (g > 0.0) bhi = u; else blo = u;
     const double f = integrand(a, mt, ser, u);
     if (f > 0.0) {
-      // converged once the Newton step is below the tolerance (it may then round to u, which
-      // is why this is tested before the bracket)
+      // converged once the Newton step is small enough (it may then round to u, which is why
+      // this is tested before the bracket)
       const double step = g / f;
-      if (fabs(step) <= tol) {
-        u -= step;
-        break;
-      }
       u -= step;
+      if (fabs(step) <= last) break;
     } else {
       u = 0.5 * (blo + bhi);
     }
@@ -407,6 +435,8 @@ hipError_t launch_generator_trials(const DevTables* tables, int generator, doubl
       hipLaunchKernelGGL(w_panel_kernel, dim3((unsigned)((a.panels + 255) / 256)), dim3(256),
                          0, s, a);
       hipLaunchKernelGGL(w_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, a);
+      hipLaunchKernelGGL(w_edge_kernel, dim3((unsigned)((a.panels + 255) / 256)), dim3(256), 0,
+                         s, a);
     }
   }
   if (n > 0) {
