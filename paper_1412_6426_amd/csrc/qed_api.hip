@@ -328,7 +328,10 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   if (!device_geometry(&cus, P.precision, fmode, lep_kernel, block, &lep_per_cu) ||
       !device_geometry(&cus, P.precision, fmode, 0, block, &pho_per_cu))
     return QED_ERR_HIP;
+  a.cus = cus;
   a.spread = 4ll * cus;
+  // beside photons (one launch) two lepton workgroups per CU leave room for one of theirs
+  if (run_photons && !lep_ext && lep_per_cu > 2) lep_per_cu = 2;
   LaunchShape lep{P.grid_blocks > 0 ? P.grid_blocks : cus * lep_per_cu, block};
   LaunchShape pho{P.grid_blocks > 0 ? P.grid_blocks : cus * pho_per_cu, block};
   if (lep.grid > kMaxGridBlocks) lep.grid = kMaxGridBlocks;

@@ -340,6 +340,7 @@ struct StepArgs {
   int adaptive, forced, emission, pairs, push_photons, freeze_on_drop;
   int generations;  // children advanced in their birth step: generations (0: none)
   long long tile;    // particles per work chunk (0: chosen from the particle count)
+  int cus;           // compute units of the device
   long long spread;  // wavefronts that few leptons are spread over (one a SIMD)
   WorkHdr* hdr;
   long long* n0;

@@ -1,24 +1,26 @@
 // qed_step.hip -- the per-step kernels of the QED step (Sec. IV.H adaptive event generator
 // of Gonoskov et al., arXiv:1412.6426, with the Sec. V.A pair generator).
 //
-// One step is up to eight launches on the caller's stream (plus three per same-step
-// generation):
+// One step is five launches on the caller's stream, up to eight in its other forms (plus three
+// per same-step generation):
 //   prep     (1 + k wgs)    snapshot live counts, particle prefix sums over the
 //                           (instance, species) segments, space-independent fields at t_n,
 //                           zero the stats record and the arenas' count matrices;
 //   leptons  (persistent)   electrons and positrons: push, chi, emission; emitted photons
 //                           go to the wavefront's share of the photon arena;
 //   photons  (persistent)   photons: push, chi_gamma, pair-rate bound; draws below the
-//                           bound go to the wavefront's candidate list for
-//   exact    (grid-stride)  the exact pair decision; pair records go to the pair arena;
-//   scan     (1 wg/instance) arena counts -> store offsets, instance counts raised and
+//                           bound go to the wavefront's candidate list (leptons and photons
+//                           are workgroups of one launch, except with same-step children, a
+//                           generator factor, its reverse mode, or events around them) for
+//   exact    (persistent)   the exact pair decision; pair records go to the pair arena;
+//   scan     (2 wgs/instance) arena counts -> store offsets, instance counts raised and
 //                           clamped to the capacities;
 //   copy     (1 wave/source wave) arena records -> photon, electron, positron stores;
-//   reduce   (1 wave/field) per-workgroup partial stats -> the stats record (status bits
-//                           set with the counters they report);
+//   reduce   (1 wave per eight fields of 128 workgroups) per-workgroup partial stats -> the
+//                           stats record (status bits set with the counters they report);
 //   finalize (1 workgroup)  clamp counts, step index + 1.
 // Where the copy is the step's last producer (arenas on, no same-step children), its launch
-// also takes the reduce jobs and the step index, and the step is six launches.
+// also takes the reduce jobs and the step index.
 // Children land after the step-start counts, so they are first processed at step n+1.
 //
 // Work distribution: the particles alive at the step start form one index space per kernel
@@ -462,13 +464,13 @@ __device__ void wave_to_block(BlockStats& bs, const LaneCounters& c, const WaveC
 
 // After a __syncthreads: store the first `fields` fields of the workgroup's record.
 __device__ __forceinline__ void block_stats_store(const BlockStats& bs, unsigned long long* part,
-                                                  int fields) {
+                                                  int fields, int block) {
   for (int i = threadIdx.x; i < fields; i += blockDim.x) {
     unsigned long long v = bs.w[i];
     if (i == kPfEnergy) v = (unsigned long long)__double_as_longlong(bs.energy);
     if (i == kPfMaxP) v = (unsigned long long)__double_as_longlong(bs.maxp);
     if (i == kPfMaxQ) v = (unsigned long long)__double_as_longlong(bs.maxq);
-    part[part_index(i, (int)blockIdx.x)] = v;
+    part[part_index(i, block)] = v;
   }
 }
 
@@ -533,11 +535,19 @@ __device__ __forceinline__ long long wave_uniform(long long v) {
   return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
-// Wavefront index within the launch (wavefront-uniform).
-__device__ __forceinline__ int wave_index() {
-  return (int)blockIdx.x * (int)(blockDim.x >> 6) +
+// A workgroup's place among those that share its work: the launch's, or those of its kind
+// where one launch advances leptons and photons.
+struct Place {
+  int block, grid;
+};
+__device__ __forceinline__ Place launch_place() { return {(int)blockIdx.x, (int)gridDim.x}; }
+
+// Wavefront index among them (wavefront-uniform).
+__device__ __forceinline__ int wave_index(Place at) {
+  return at.block * (int)(blockDim.x >> 6) +
          __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 }
+__device__ __forceinline__ int wave_index() { return wave_index(launch_place()); }
 
 // Per-wavefront tally of arena records per instance.  Records are counted for the instance
 // `cur` in a register; when another instance shows up the tally goes to the wavefront's own
@@ -675,11 +685,9 @@ struct TileCursor {
 struct WaveRange {
   long long g, gend, chunk, T, W, N;
 
-  __device__ __forceinline__ void init(long long n, long long tile, long long spread) {
-    const long long wpb = blockDim.x >> 6;
-    W = (long long)gridDim.x * wpb;
-    const long long wv = (long long)blockIdx.x * wpb +
-                         __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  __device__ __forceinline__ void init(Place at, long long n, long long tile, long long spread) {
+    W = (long long)at.grid * (blockDim.x >> 6);
+    const long long wv = wave_index(at);
     N = n;
     T = chunk_size(N, W, tile, spread);
     chunk = wv - W;
@@ -732,9 +740,9 @@ __device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, lo
                   : 0;
 }
 // Does this workgroup own any work?
-__device__ __forceinline__ bool block_has_work(long long N, long long tile, long long spread) {
-  return (int)blockIdx.x <
-         working_blocks(N, (int)gridDim.x, (int)(blockDim.x >> 6), tile, spread);
+__device__ __forceinline__ bool block_has_work(Place at, long long N, long long tile,
+                                               long long spread) {
+  return at.block < working_blocks(N, at.grid, (int)(blockDim.x >> 6), tile, spread);
 }
 
 template <bool MIXED>
@@ -999,20 +1007,28 @@ struct LeptonShape {
       global_table || (MIXED && FMODE != kFieldLocal && !EXT) ? 3 : EXT ? 2 : 1;
 };
 
+// The lepton kernels' LDS.
+template <bool MIXED, int FMODE, bool EXT>
+struct LeptonLds {
+  typename TabType<MIXED>::T tab[LeptonShape<MIXED, FMODE, EXT>::global_table ? 1 : kTableN];
+  BlockStats bs;
+  MathTab mt;
+  PhotonStage stage[kWavesPerBlock];
+};
+
 // RUNS: the reverse mode of Sec. VI (runs_photon > 1) is compiled in (with EXT).
 template <bool MIXED, int FMODE, bool EXT, bool RUNS>
-__device__ __forceinline__ void lepton_step(const StepArgs& a) {
+__device__ __forceinline__ void lepton_step(const StepArgs& a, Place at,
+                                            LeptonLds<MIXED, FMODE, EXT>& lds) {
   using Tab = typename TabType<MIXED>::T;
   constexpr bool kGlobalTab = LeptonShape<MIXED, FMODE, EXT>::global_table;
-  __shared__ Tab tab_lds[kGlobalTab ? 1 : kTableN];
-  __shared__ BlockStats bs;
-  __shared__ MathTab mt;
-  __shared__ PhotonStage stage[kWavesPerBlock];
+  BlockStats& bs = lds.bs;
+  MathTab& mt = lds.mt;
   const MathRow mrow = load_math();
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->lep_total;
-  const int wid = wave_index();
-  if (!block_has_work(N, a.tile, a.spread)) {
+  const int wid = wave_index(at);
+  if (!block_has_work(at, N, a.tile, a.spread)) {
     if (a.pa.waves > 0 && lane_id() == 0) a.pa.nrec[wid] = 0u;
     return;
   }
@@ -1020,8 +1036,8 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   const Tab* src = MIXED ? reinterpret_cast<const Tab*>(a.tables->ab32)
                          : reinterpret_cast<const Tab*>(a.tables->ab64);
   if (!kGlobalTab)
-    for (int i = threadIdx.x; i < kTableN; i += blockDim.x) tab_lds[i] = src[i];
-  const Tab* tab = kGlobalTab ? src : tab_lds;
+    for (int i = threadIdx.x; i < kTableN; i += blockDim.x) lds.tab[i] = src[i];
+  const Tab* tab = kGlobalTab ? src : lds.tab;
   store_math(mt, mrow);
   __syncthreads();
 
@@ -1034,14 +1050,14 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
   FieldArgs fld = a.field;
   fld.tn = hdr->tn;
   const uint64_t below = lanes_below();
-  PhotonStage& sg = stage[threadIdx.x >> 6];
+  PhotonStage& sg = lds.stage[threadIdx.x >> 6];
 
   LaneCounters cnt;
   cnt.bs = &bs;
   WaveCounters wc;
   TileCursor tc;
   WaveRange wr;
-  wr.init(N, a.tile, a.spread);
+  wr.init(at, N, a.tile, a.spread);
   bool open = true;
   int staged = 0;
   // arena: this wavefront's share, then pool chunks
@@ -1326,14 +1342,15 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a) {
 
   wave_to_block(bs, cnt, wc);
   __syncthreads();
-  block_stats_store(bs, a.lep_part, kPfCount);
+  block_stats_store(bs, a.lep_part, kPfCount, at.block);
 }
 
 template <bool MIXED, int FMODE, bool EXT>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(LeptonShape<MIXED, FMODE, EXT>::min_waves)))
     lepton_kernel(StepArgs a) {
-  lepton_step<MIXED, FMODE, EXT, false>(a);
+  __shared__ LeptonLds<MIXED, FMODE, EXT> lds;
+  lepton_step<MIXED, FMODE, EXT, false>(a, launch_place(), lds);
 }
 
 // The reverse mode of Sec. VI in a kernel of its own: its extra runs hold more registers,
@@ -1342,7 +1359,8 @@ __global__ void __launch_bounds__(256)
 template <bool MIXED, int FMODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     lepton_runs_kernel(StepArgs a) {
-  lepton_step<MIXED, FMODE, true, true>(a);
+  __shared__ LeptonLds<MIXED, FMODE, true> lds;
+  lepton_step<MIXED, FMODE, true, true>(a, launch_place(), lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1485,14 +1503,19 @@ __device__ __forceinline__ PhotonIn load_photons(const qed_soa& S, long long bas
   return r;
 }
 
+struct PhotonLds {
+  BlockStats bs;
+  double bound[kBoundEntries];
+};
+
 template <bool MIXED, int FMODE>
-__global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
-  __shared__ BlockStats bs;
-  __shared__ double sbound[kBoundEntries];
+__device__ __forceinline__ void photon_step(const StepArgs& a, Place at, PhotonLds& lds) {
+  BlockStats& bs = lds.bs;
+  double* const sbound = lds.bound;
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->pho_total;
-  const int wid = wave_index();
-  if (!block_has_work(N, a.tile, 0)) return;
+  const int wid = wave_index(at);
+  if (!block_has_work(at, N, a.tile, 0)) return;
   block_stats_init(bs);
   stage_bounds<MIXED>(a, sbound);
   __syncthreads();
@@ -1511,7 +1534,7 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   WaveCounters wc;
   TileCursor tc;
   WaveRange wr;
-  wr.init(N, a.tile, 0);
+  wr.init(at, N, a.tile, 0);
 
   // Software pipeline: the next 64 photons' columns (in this piece or the next one) are
   // requested before the current ones are processed, so each wavefront keeps a load batch
@@ -1618,7 +1641,58 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   if (lane == 0) a.candn[wid] = (unsigned)ncand;
   wave_to_block(bs, cnt, wc);
   __syncthreads();
-  block_stats_store(bs, a.pho_part, kPfNsub);
+  block_stats_store(bs, a.pho_part, kPfNsub, at.block);
+}
+
+template <bool MIXED, int FMODE>
+__global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
+  __shared__ PhotonLds lds;
+  photon_step<MIXED, FMODE>(a, launch_place(), lds);
+}
+
+// Leptons and photons of a step in one launch (no same-step children): neither reads what the
+// other writes.  The leptons' arithmetic and the photons' memory traffic share the CUs, the tail
+// of one is filled by the other, and a launch is saved.  The workgroups go out in groups of one
+// per CU (a multiple of the XCDs, so that a workgroup's XCD stays its index modulo 8): the
+// leptons first, two per CU, beside one of photons at a time and then three.  Where the photons
+// are most of the work (kInterleave times the leptons or more) and bound by memory, one group of
+// leptons, two of photons, in turn, which keeps loads in flight beside both halves of the
+// leptons.  Against a launch each, same device: 64-electron cascade 3124 to 2860 us, mixed
+// cascade 28.0 to 26.2 ms, 64 mixed instances 14.4 to 12.7, grid cascade 35.3 to 32.3, largest
+// rotating cascade 141 to 134.  Leptons first throughout: 139; in turn throughout: 64 instances
+// 13.3, grid 33.3; three lepton workgroups per CU: largest 141 to 148.
+constexpr long long kInterleave = 8;
+template <bool MIXED, int FMODE>
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(LeptonShape<MIXED, FMODE, false>::min_waves)))
+    particle_kernel(StepArgs a, int lep_grid, int pho_grid) {
+  __shared__ union Lds {
+    LeptonLds<MIXED, FMODE, false> lep;
+    PhotonLds pho;
+    __device__ Lds() {}
+  } lds;
+  // cycles of one group of lepton workgroups and `per` of photon ones; then the other leptons,
+  // then the other photons
+  const int b = (int)blockIdx.x, group = a.cus;
+  const int per = max(pho_grid / max(lep_grid, 1), 1);
+  const int cycles = a.hdr->pho_total >= kInterleave * a.hdr->lep_total
+                         ? min(lep_grid / group, pho_grid / (group * per))
+                         : 0;
+  Place at;
+  bool lep;
+  const int r = b - cycles * (1 + per) * group;
+  if (r < 0) {
+    const int g = b / group, c = g / (1 + per), w = g - c * (1 + per);
+    lep = w == 0;
+    at.block = (lep ? c : c * per + w - 1) * group + (b - g * group);
+  } else {
+    const int more = lep_grid - cycles * group;
+    lep = r < more;
+    at.block = lep ? cycles * group + r : cycles * per * group + (r - more);
+  }
+  at.grid = lep ? lep_grid : pho_grid;
+  if (lep) lepton_step<MIXED, FMODE, false, false>(a, at, lds.lep);
+  else photon_step<MIXED, FMODE>(a, at, lds.pho);
 }
 
 // State of one wavefront of the exact pair-decision kernel.
@@ -1955,7 +2029,7 @@ __device__ __forceinline__ void exact_pass(const StepArgs& a) {
   }
   wave_to_block(bs, cnt, wc);
   __syncthreads();
-  block_stats_store(bs, a.ex_part, kPfNsub);
+  block_stats_store(bs, a.ex_part, kPfNsub, (int)blockIdx.x);
 }
 
 template <bool MIXED, int FMODE>
@@ -2409,7 +2483,7 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
     Kin kn{0.0, 0.0, {1.0, 1.0, true}};
     bool first = false;
     double delta1 = 0.0;
-    for (;;) {  // (until a lane emits or ends its last sub-step, as in lepton_kernel)
+    for (;;) {  // (until a lane emits or ends its last sub-step, as in lepton_step)
       if (slot >= 0) {
         first = lepton_substep<MIXED, FMODE != kFieldE>(a, tab, mt, ser64, ser32, id, seed,
                                                         step, refine, L, kn, bs, cnt, delta1);
@@ -2419,7 +2493,7 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
       ++k;
       --left;
     }
-    // the emission generator, N_g times in the reverse mode of Sec. VI (as in lepton_kernel)
+    // the emission generator, N_g times in the reverse mode of Sec. VI (as in lepton_step)
     const int runs = RUNS ? a.runs_photon : 1;
     const double wrun = wgt / (double)runs;
     V3 rec = {0.0, 0.0, 0.0};
@@ -2780,21 +2854,30 @@ __global__ void __launch_bounds__(256) gen_runs_kernel(StepArgs a, GenArgs q) {
 template <bool MIXED, int FMODE>
 static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape pho,
                               bool run_photons, hipStream_t s) {
+  // one launch for both kinds, unless the caller times them apart
+  const bool ext = a.generations > 0 || a.fg_photon > 1.0;
+  bool fused = run_photons && !ext && a.runs_photon <= 1;
+  for (int i = 0; i < 4; ++i) fused = fused && !a.events[i];
   if (a.events[0]) (void)hipEventRecord(a.events[0], s);
-  if (a.runs_photon > 1)
+  if (fused)
+    hipLaunchKernelGGL((particle_kernel<MIXED, FMODE>), dim3(lep.grid + pho.grid),
+                       dim3(lep.block), 0, s, a, lep.grid, pho.grid);
+  else if (a.runs_photon > 1)
     hipLaunchKernelGGL((lepton_runs_kernel<MIXED, FMODE>), dim3(lep.grid), dim3(lep.block), 0,
                        s, a);
-  else if (a.generations > 0 || a.fg_photon > 1.0)
+  else if (ext)
     hipLaunchKernelGGL((lepton_kernel<MIXED, FMODE, true>), dim3(lep.grid), dim3(lep.block), 0,
                        s, a);
   else
     hipLaunchKernelGGL((lepton_kernel<MIXED, FMODE, false>), dim3(lep.grid), dim3(lep.block), 0,
                        s, a);
   if (a.events[1]) (void)hipEventRecord(a.events[1], s);
-  if (run_photons) {
+  if (run_photons && !fused) {
     if (a.events[2]) (void)hipEventRecord(a.events[2], s);
     hipLaunchKernelGGL((photon_kernel<MIXED, FMODE>), dim3(pho.grid), dim3(pho.block), 0, s, a);
     if (a.events[3]) (void)hipEventRecord(a.events[3], s);
+  }
+  if (run_photons) {
     if (a.ex_grid > 0 && a.runs_pair > 1)
       hipLaunchKernelGGL((photon_exact_runs_kernel<MIXED, FMODE>), dim3(a.ex_grid), dim3(256), 0,
                          s, a);
