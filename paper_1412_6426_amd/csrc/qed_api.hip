@@ -330,8 +330,10 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
     return QED_ERR_HIP;
   a.cus = cus;
   a.spread = 4ll * cus;
-  // beside photons (one launch) two lepton workgroups per CU leave room for one of theirs
-  if (run_photons && !lep_ext && lep_per_cu > 2) lep_per_cu = 2;
+  // beside photons (one launch, no events) two lepton workgroups per CU leave room for one of
+  // theirs; a launch of their own takes all it can hold
+  const bool apart = a.events[0] || a.events[1] || a.events[2] || a.events[3];
+  if (run_photons && !lep_ext && !apart && lep_per_cu > 2) lep_per_cu = 2;
   LaunchShape lep{P.grid_blocks > 0 ? P.grid_blocks : cus * lep_per_cu, block};
   LaunchShape pho{P.grid_blocks > 0 ? P.grid_blocks : cus * pho_per_cu, block};
   if (lep.grid > kMaxGridBlocks) lep.grid = kMaxGridBlocks;
