@@ -892,14 +892,15 @@ __host__ __device__ inline int finish_parts(long long slots, int n_inst) {
   return p < 1 ? 1 : p > 256 ? 256 : (int)p;
 }
 
-// Sums over the groups of instance blockIdx.y, part blockIdx.x of them (fixed-order
-// reductions): one workgroup over a grid's groups took 390 us for 3 10^5 of them.
-__global__ void __launch_bounds__(kSortThreads) thin_sums_kernel(SortArgs a, ThinArgs t) {
+// Sums over one of the P parts of one instance's groups, a workgroup each, the parts of an
+// instance next to each other (one dimension: a grid's y extent ends at 65535 instances).
+// Fixed-order reductions; one workgroup over a grid's groups took 390 us for 3 10^5 of them.
+__global__ void __launch_bounds__(kSortThreads) thin_sums_kernel(SortArgs a, ThinArgs t, int P) {
   __shared__ double sd[2][kSortThreads];
   __shared__ long long sl[3][kSortThreads];
-  const int i = blockIdx.y, P = (int)gridDim.x;
+  const int i = (int)(blockIdx.x / (unsigned)P), part = (int)(blockIdx.x % (unsigned)P);
   const long long q0 = t.gpfx[i], q1 = t.gpfx[i + 1], len = (q1 - q0 + P - 1) / P;
-  const long long lo = q0 + (long long)blockIdx.x * len, hi = lo + len < q1 ? lo + len : q1;
+  const long long lo = q0 + (long long)part * len, hi = lo + len < q1 ? lo + len : q1;
   double wb = 0.0, wa = 0.0;
   long long live = 0, groups = 0, thinned = 0;
   for (long long q = lo + threadIdx.x; q < hi; q += blockDim.x) {
@@ -926,7 +927,7 @@ __global__ void __launch_bounds__(kSortThreads) thin_sums_kernel(SortArgs a, Thi
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    double* p = t.part + kPartWords * ((size_t)i * P + blockIdx.x);
+    double* p = t.part + kPartWords * (size_t)blockIdx.x;
     p[0] = sd[0][0];
     p[1] = sd[1][0];
     for (int k = 0; k < 3; ++k) p[2 + k] = (double)sl[k][0];  // below 2^32
@@ -1094,7 +1095,8 @@ hipError_t launch_thin_cells(const qed_soa& s, int species, qed_instance* inst, 
   hipLaunchKernelGGL(thin_keep_kernel, dim3(grid), blk, 0, st, a, t);
   hipLaunchKernelGGL(thin_scan_kernel, dim3(1), blk, 0, st, a, t, 1);
   hipLaunchKernelGGL(thin_store_kernel, dim3(grid), blk, 0, st, a, t);
-  hipLaunchKernelGGL(thin_sums_kernel, dim3((unsigned)parts, (unsigned)n_inst), blk, 0, st, a, t);
+  hipLaunchKernelGGL(thin_sums_kernel, dim3((unsigned)parts * (unsigned)n_inst), blk, 0, st, a, t,
+                     parts);
   hipLaunchKernelGGL(thin_finish_kernel, dim3((unsigned)((n_inst + 3) / 4)), blk, 0, st, a, t,
                      parts);
   return hipGetLastError();
