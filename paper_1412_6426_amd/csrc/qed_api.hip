@@ -258,7 +258,8 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   a.dt = P.dt;
   a.t0 = P.t0;
   a.eps_r = P.eps_r;
-  a.inv_eps_r = 1.0 / P.eps_r;
+  a.z_scale = (double)(2.25L * (long double)P.eps_r * (long double)P.eps_r);
+  if (!isnormal(a.z_scale)) a.z_scale = INFINITY;
   a.inv_lep_scale = 1.0 / (P.kappa * 28.0 * kPi * P.eps_r);
   a.inv_pho_scale = 1.0 / (P.kappa * 260.0 * kPi * P.eps_r);
   a.dtfac_per_h = kAlpha / P.eps_r;

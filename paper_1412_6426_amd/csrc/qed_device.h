@@ -141,7 +141,7 @@ struct Series64 {
 
 // The two tabulated functions at kZLo <= z < kZHi, times e^z and combined as x + cB y.
 __device__ __forceinline__ double2 table_at(const double2* tab, const MathTab& mt, double z) {
-  const double u = (log2_normal(mt, z) - kLog2ZLo) * kNodesPerLog2;
+  const double u = log2_affine(mt, z, (int)kLog2ZLo, kNodesPerLog2, 0.0);
   const int i = min((int)u, kTableN - 2);
   const double f = u - (double)i;
   const double2 g0 = tab[i];
@@ -149,13 +149,13 @@ __device__ __forceinline__ double2 table_at(const double2* tab, const MathTab& m
   return make_double2(g0.x + f * (g1.x - g0.x), g0.y + f * (g1.y - g0.y));
 }
 
-// z^(2/3) of the small-z series (below the normal range, the library's cube root).
-__device__ __forceinline__ double series_z23(const MathTab& mt, double z) {
-  return z >= kFastLo ? pow23_normal(mt, z) : cbrt(z * z);
+// x^(2/3) of any x >= 0 (beyond the range of pow23_normal, the library's cube root).
+__device__ __forceinline__ double pow23(const MathTab& mt, double x) {
+  return x >= kPow23Lo && x <= kPow23Hi ? pow23_normal(mt, x) : cbrt(x * x);
 }
 __device__ __forceinline__ void series_bc(const MathTab& mt, const Series64& s, double z,
                                           double& b, double& c) {
-  const double z23 = series_z23(mt, z);
+  const double z23 = pow23(mt, z);
   const double z43 = z23 * z23;
   b = s.b0 / z23 + s.b1 * z23 + 0.75 * s.b0 * z43;
   c = s.c0 - s.c1 * z23 - s.c2 * z43;
@@ -369,8 +369,7 @@ __device__ __forceinline__ void push_any(const V3& p0, double qh2, const V3& E, 
 __device__ __forceinline__ double substep_ratio_lepton(const MathTab& mt, double dt, const Kin& k,
                                                        double eps_r, double inv_lep_scale) {
   const double r = k.g.under(eps_r * root_of(k.c2).r);  // chi / gamma
-  const double r23 = (r >= kFastLo && r <= kFastHi) ? pow23_normal(mt, r) : cbrt(r * r);
-  return dt * r23 * inv_lep_scale;  // inv_lep_scale = 1/(kappa 28 pi eps_r)
+  return dt * pow23(mt, r) * inv_lep_scale;  // inv_lep_scale = 1/(kappa 28 pi eps_r)
 }
 // (h / (kappa 28 pi eps_r))^3: a sub-step of length h satisfies Eq. (29) in a state of
 // (chi, gamma) iff this times chi^2 is at most gamma^2 (no cube root on the sub-step path).

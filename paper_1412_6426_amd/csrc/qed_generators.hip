@@ -44,9 +44,9 @@ struct TrialArgs {
 __device__ __forceinline__ double density(const TrialArgs& a, const MathTab& mt,
                                           const Series64& ser, double d) {
   if (!(d > 0.0 && d < 1.0)) return 0.0;
-  const double iomd = rcp_normal(1.0 - d);
-  const double z = a.z_per_q * (d * iomd);
-  return a.pref * emission_bracket64(a.tables->ab64, mt, ser, z, d * d * iomd);
+  const double omd = 1.0 - d;
+  const double q = div_normal(d, omd, rcp_normal(omd));
+  return a.pref * emission_bracket64(a.tables->ab64, mt, ser, a.z_per_q * q, d * q);
 }
 
 // W's integrand in u.
@@ -417,7 +417,7 @@ hipError_t launch_generator_trials(const DevTables* tables, int generator, doubl
   a.chi = chi;
   a.gamma = gamma;
   a.dtfac = dtfac;
-  a.z_per_q = (2.0 / 3.0) / chi;
+  a.z_per_q = (double)(2.0L / (3.0L * (long double)chi));
   a.pref = dtfac * kInvSqrt3Pi / gamma;
   a.key0 = (uint32_t)key;
   a.key1 = (uint32_t)(key >> 32);

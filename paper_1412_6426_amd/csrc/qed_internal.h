@@ -326,7 +326,8 @@ struct StepArgs {
   const DevTables* tables;
   FieldArgs field;
   double e0[3], b0[3];
-  double dt, t0, eps_r, inv_eps_r;
+  double dt, t0, eps_r;
+  double z_scale;        // (3/2 eps_r)^2; infinity where that is no normal number
   double inv_lep_scale;  // 1 / (kappa 28 pi eps_r)
   double inv_pho_scale;  // 1 / (kappa 260 pi eps_r)
   double dtfac_per_h;    // alpha / eps_r

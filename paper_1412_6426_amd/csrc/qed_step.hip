@@ -754,10 +754,11 @@ struct TabType<true> {
   using T = float2;
 };
 
-// One draw of the modified generator (Sec. IV.G): r1, r2, delta = r1^3 and 1 / (1 - delta).
+// One draw of the modified generator (Sec. IV.G): r1, r2, delta = r1^3 and
+// q = delta / (1 - delta).
 struct EmissionDraw {
-  double r1, r2, d, iomd;  // FP64 form
-  float f1, f2, fd;        // mixed form
+  double r1, r2, d, q;  // FP64 form
+  float f1, f2, fd;     // mixed form
 };
 template <bool MIXED>
 __device__ __forceinline__ EmissionDraw emission_draw(const uint4& o) {
@@ -770,28 +771,25 @@ __device__ __forceinline__ EmissionDraw emission_draw(const uint4& o) {
     e.r1 = uniform64(o.x, o.y);
     e.r2 = uniform64(o.z, o.w);
     e.d = e.r1 * e.r1 * e.r1;
-    e.iomd = rcp_normal(1.0 - e.d);  // 1 - delta >= 2^-52
+    const double omd = 1.0 - e.d;  // >= 2^-52
+    e.q = div_normal(e.d, omd, rcp_normal(omd));
   }
   return e;
 }
 
 // Emission decision (Eqs. (24), (25)): emit iff r2 < 3 r1^2 P(r1^3).  The mixed form evaluates
-// the rate and the comparison in FP32.  One reciprocal of 1 - delta and one of chi (from its
-// square) serve z = (2/3) delta / ((1 - delta) chi) and delta^2 / (1 - delta), and 1 / gamma
-// comes with the state: 0.75 of the time of six divisions and roots.
+// the rate and the comparison in FP32.  In FP64, with z_scale = (3/2 eps_r)^2, one inverse root
+// gives z = (2/3) q / chi = q / sqrt(z_scale c2): at most 4.2 units of 2^-53 from the draw's
+// and the state's exact z, where root, products and division had 6 (P takes z times that).
 template <bool MIXED>
 __device__ __forceinline__ bool emission_decision(const typename TabType<MIXED>::T* tab,
                                                   const MathTab& mt, const Series64& ser64,
                                                   const Series32& ser32, const EmissionDraw& e,
-                                                  const Kin& kn, double eps_r, double inv_eps_r,
+                                                  const Kin& kn, double eps_r, double z_scale,
                                                   double dtfac, LaneCounters& cnt,
                                                   double& delta) {
-  // chi = 0 is taken as 2^-450 eps_r: z is beyond the tabulated range and P = 0 either way
-  const double c2 = fmax(kn.c2, kFastLo);
-  const double rc = rsqrt_normal(c2);
-  const bool fast = kn.g.fast && c2 <= kFastHi;
   if (MIXED) {
-    const float chi = (float)(eps_r * (fast ? sqrt_from_rsqrt(c2, rc) : sqrt(kn.c2)));
+    const float chi = (float)(eps_r * root_of(kn.c2).r);
     const float r1 = e.f1, r2 = e.f2;
     const float d = e.fd, omd = 1.0f - d;
     const float z = (2.0f / 3.0f) * d / (omd * chi);
@@ -803,15 +801,18 @@ __device__ __forceinline__ bool emission_decision(const typename TabType<MIXED>:
     return r2 < P;
   }
   const double d = e.d;
-  double z = (2.0 / 3.0) * (d * e.iomd) * inv_eps_r * rc;
-  double pg = dtfac * kInvSqrt3Pi * kn.g.inv;
-  if (!fast) {
-    z = (2.0 / 3.0) * (d * e.iomd) / (eps_r * sqrt(kn.c2));
+  // a field of 0 is taken as 2^-450 (z_scale infinite: as any): z is beyond the tabulated range
+  // and P = 0 either way
+  const double w = fmax(z_scale * kn.c2, kFastLo);
+  double z = e.q * rsqrt_normal(w);
+  double pg = div_normal(dtfac * kInvSqrt3Pi, kn.g.r, kn.g.inv);
+  if (!(kn.g.fast && w <= kFastHi)) {
+    z = (2.0 / 3.0) * d / ((1.0 - d) * (eps_r * sqrt(kn.c2)));
     pg = kn.g.under(dtfac * kInvSqrt3Pi);
   }
   const double P = 3.0 * e.r1 * e.r1 * pg *
                    emission_bracket64(reinterpret_cast<const double2*>(tab), mt, ser64, z,
-                                      d * d * e.iomd);
+                                      d * e.q);
   cnt.note(P, e.r2);
   delta = d;
   return e.r2 < P;
@@ -856,7 +857,7 @@ __device__ __forceinline__ bool lepton_substep(const StepArgs& a,
   }
   L.x = axpy(kn.g.under(L.h), L.p, L.x);
   if (!a.emission) return false;
-  return emission_decision<MIXED>(tab, mt, ser64, ser32, e, kn, a.eps_r, a.inv_eps_r, L.dtfac,
+  return emission_decision<MIXED>(tab, mt, ser64, ser32, e, kn, a.eps_r, a.z_scale, L.dtfac,
                                   cnt, delta);
 }
 
@@ -874,8 +875,9 @@ __device__ __forceinline__ bool emission_photon(const MathTab& mt, const Kin& kn
   f = root_of(kn.p2).under(eps);
   // bin floor(10 (log10 eps + 8)), in FP64 in both precisions (an emission is rare next to
   // the sub-steps, and the bins then agree with an FP64 count of the same photons)
-  const double l2 = (eps >= kFastLo && eps <= kFastHi) ? log2_normal(mt, eps) : log2(eps);
-  const double lb = floor(fma(l2, 10.0 * kLog10Of2, 80.0));
+  const double s10 = 10.0 * kLog10Of2;
+  const double lb = floor(eps >= kFastLo && eps <= kFastHi ? log2_affine(mt, eps, 0, s10, 80.0)
+                                                           : fma(log2(eps), s10, 80.0));
   if (lb >= 0.0 && lb < (double)QED_SPECTRUM_BINS) atomicAdd(&bs.w[kPfHist + (int)lb], 1ull);
   cnt.energy += wgt * eps;
   return true;
@@ -1260,7 +1262,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a, Place at,
           const uint4 o = draw_words(id, seed, step, sc, kDraw);
           double delta;
           e2 = emission_decision<MIXED>(tab, mt, ser64, ser32, emission_draw<MIXED>(o), kn,
-                                        a.eps_r, a.inv_eps_r, L.dtfac, cnt, delta);
+                                        a.eps_r, a.z_scale, L.dtfac, cnt, delta);
           if (e2) {
             e2 = emission_photon(mt, kn, delta, wrun, bs, cnt, f2);
             if (e2) ++nev;
@@ -1473,9 +1475,9 @@ __device__ __forceinline__ bool pair_decision(const StepArgs& a, const MathTab& 
   }
   const double r1 = uniform64(o.x, o.y), r2 = uniform64(o.z, o.w);
   const double omd = 1.0 - r1;  // r1 and 1 - r1 >= 2^-53
-  const double iv = rcp_normal(r1 * omd);
-  const double z = (2.0 / 3.0) * iv / chi;
-  const double P = pref * pair_bracket64(a.tables->bc64, mt, s64, z, (r1 * r1 + omd * omd) * iv);
+  const double z = (2.0 / 3.0) / (chi * r1 * omd);
+  const double cB = div_normal(r1, omd, rcp_normal(omd)) + div_normal(omd, r1, rcp_normal(r1));
+  const double P = pref * pair_bracket64(a.tables->bc64, mt, s64, z, cB);
   cnt.note(P, r2, r2 < P);
   *r1out = r1;
   return r2 < P;
@@ -2509,7 +2511,7 @@ __device__ __forceinline__ void gen_lepton_phase(const StepArgs& a, const GenArg
         else
           emit = emission_decision<MIXED>(
               tab, mt, ser64, ser32, emission_draw<MIXED>(draw_words(id, seed, step, sc, kDraw)),
-              kn, a.eps_r, a.inv_eps_r, L.dtfac, cnt, delta);
+              kn, a.eps_r, a.z_scale, L.dtfac, cnt, delta);
         if (emit) {
           emit = emission_photon(mt, kn, delta, wrun, bs, cnt, f);
           if (emit) ++nev;
