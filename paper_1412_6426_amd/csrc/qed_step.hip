@@ -535,6 +535,13 @@ __device__ __forceinline__ long long wave_uniform(long long v) {
   return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
+__device__ __forceinline__ double wave_uniform(double v) {
+  return __longlong_as_double(wave_uniform((long long)__double_as_longlong(v)));
+}
+__device__ __forceinline__ V3 wave_uniform(const V3& v) {
+  return {wave_uniform(v.x), wave_uniform(v.y), wave_uniform(v.z)};
+}
+
 // A workgroup's place among those that share its work: the launch's, or those of its kind
 // where one launch advances leptons and photons.
 struct Place {
@@ -693,9 +700,8 @@ struct WaveRange {
     chunk = wv - W;
     g = gend = 0;
   }
-  // Next piece within one segment; false once the wavefront's share is exhausted.
-  __device__ __forceinline__ bool next(const StepArgs& a, const long long* pref, int nseg,
-                                       bool lepton, TileCursor& tc) {
+  // At particle g of a chunk; false once the wavefront's share is exhausted.
+  __device__ __forceinline__ bool more() {
     while (g >= gend) {
       chunk += W;
       const long long s = chunk * T;
@@ -703,6 +709,12 @@ struct WaveRange {
       g = s;
       gend = min(s + T, N);
     }
+    return true;
+  }
+  // Next piece within one segment.
+  __device__ __forceinline__ bool next(const StepArgs& a, const long long* pref, int nseg,
+                                       bool lepton, TileCursor& tc) {
+    if (!more()) return false;
     int lo = 0, hi = nseg;  // pref[lo] <= g < pref[hi]
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -1483,25 +1495,23 @@ __device__ __forceinline__ bool pair_decision(const StepArgs& a, const MathTab& 
   return r2 < P;
 }
 
-// Columns of up to 64 photon slots [base, end) for one wavefront (lane i takes base + i;
-// lanes past the end get a dead id).  `base` is wavefront-uniform, so every column is
+// Columns of the n <= 64 photon slots from `base` on for one wavefront (lane i takes base + i,
+// the lanes from n on the last one's again).  `base` is wavefront-uniform, so every column is
 // addressed by one scalar base and a lane offset.
 struct PhotonIn {
   uint64_t id;
   V3 x, k;
 };
-__device__ __forceinline__ PhotonIn load_photons(const qed_soa& S, long long base, long long end,
+__device__ __forceinline__ PhotonIn load_photons(const qed_soa& S, long long base, int n,
                                                  int lane) {
-  PhotonIn r{QED_ID_DEAD, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-  if (lane < end - base) {
-    // the columns this kernel only reads are streamed past the caches (non-temporal): 3%
-    // faster; the positions, which it writes back, are slower read that way
-    r.id = __builtin_nontemporal_load(&S.id[base + lane]);
-    r.x = {S.x[base + lane], S.y[base + lane], S.z[base + lane]};
-    r.k = {__builtin_nontemporal_load(&S.px[base + lane]),
-           __builtin_nontemporal_load(&S.py[base + lane]),
-           __builtin_nontemporal_load(&S.pz[base + lane])};
-  }
+  PhotonIn r;
+  const int i = min(lane, n - 1);
+  // the columns this kernel only reads are streamed past the caches (non-temporal): 3%
+  // faster; the positions, which it writes back, are slower read that way
+  r.id = __builtin_nontemporal_load(&S.id[base + i]);
+  r.x = {S.x[base + i], S.y[base + i], S.z[base + i]};
+  r.k = {__builtin_nontemporal_load(&S.px[base + i]), __builtin_nontemporal_load(&S.py[base + i]),
+         __builtin_nontemporal_load(&S.pz[base + i])};
   return r;
 }
 
@@ -1510,7 +1520,56 @@ struct PhotonLds {
   double bound[kBoundEntries];
 };
 
-template <bool MIXED, int FMODE>
+// One batch of a photon wavefront: the n slots from `base` on, requested but not waited for
+// (n = 0: the wavefront has no more).
+struct PhotonBatch {
+  PhotonIn in;
+  long long base = 0, g = 0;  // slot and index in the kernel's particle index space
+  int n = 0, inst = 0;
+};
+// A photon wavefront's batches in turn.  Loads come back in their order, and the compiler waits
+// for as many as the path with the fewest has issued: so every fetch issues its loads, the ones
+// past the end those of the last batch again (or of slot 0), and an instance's segment is looked
+// up once for all the pieces in it.
+struct PhotonStream {
+  WaveRange wr;
+  long long pos = 0, end = 0;      // slots of the current piece
+  long long seg_end = 0, off = 0;  // end of the current segment, slot - index in it
+  long long last = 0;              // first slot of the last batch
+  int inst = 0;
+  __device__ __forceinline__ void fetch(const StepArgs& a, const qed_soa& S, int lane,
+                                        PhotonBatch& b) {
+    if (pos >= end && wr.more()) {
+      if (wr.g >= seg_end) {
+        int lo = 0, hi = a.n_inst;  // pho_pref[lo] <= g < pho_pref[hi]
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (wave_uniform(a.pho_pref[mid]) <= wr.g) lo = mid;
+          else hi = mid;
+        }
+        inst = lo;
+        seg_end = wave_uniform(a.pho_pref[lo + 1]);
+        off = wave_uniform(a.inst[lo].base[QED_PHOTON] - a.pho_pref[lo]);
+      }
+      pos = wr.g + off;
+      wr.g = min(wr.gend, seg_end);
+      end = wr.g + off;
+    }
+    b.n = (int)min(end - pos, 64ll);
+    if (b.n > 0) last = pos;
+    b.base = last;
+    b.g = last - off;
+    b.inst = inst;
+    // the loads go out at a raised wave priority, ahead of the other wavefronts' arithmetic on
+    // the SIMD (265 against 267 us per launch on the rotating-field cascade)
+    __builtin_amdgcn_s_setprio(1);
+    b.in = load_photons(S, last, max(b.n, 1), lane);
+    __builtin_amdgcn_s_setprio(0);
+    pos += b.n;
+  }
+};
+
+template <bool MIXED, int FMODE, int DEPTH>
 __device__ __forceinline__ void photon_step(const StepArgs& a, Place at, PhotonLds& lds) {
   BlockStats& bs = lds.bs;
   double* const sbound = lds.bound;
@@ -1534,111 +1593,120 @@ __device__ __forceinline__ void photon_step(const StepArgs& a, Place at, PhotonL
   LaneCounters cnt;
   cnt.bs = &bs;
   WaveCounters wc;
-  TileCursor tc;
-  WaveRange wr;
-  wr.init(at, N, a.tile, 0);
+  PhotonStream st;
+  st.wr.init(at, N, a.tile, 0);
 
-  // Software pipeline: the next 64 photons' columns (in this piece or the next one) are
-  // requested before the current ones are processed, so each wavefront keeps a load batch
-  // in flight while it computes.
-  bool has = wr.next(a, a.pho_pref, a.n_inst, false, tc);
-  PhotonIn nxt{};
-  if (has) nxt = load_photons(S, wave_uniform(tc.cur), wave_uniform(tc.end), lane);
-  while (has) {
-    const int inst = __builtin_amdgcn_readfirstlane(tc.inst);
-    const uint64_t seed = a.inst[inst].seed;
-    V3 E{}, B{};
-    if (FMODE != kFieldLocal) instance_fields<FMODE>(a, inst, E, B);
-    const long long cur = wave_uniform(tc.cur), end = wave_uniform(tc.end);
-    const long long g0 = wave_uniform(tc.g);
-    TileCursor tn;
-    bool has_next = false;
-    for (long long base = cur; base < end; base += 64) {
-      const PhotonIn in = nxt;
-      if (base + 64 < end) {
-        // the next batch's loads go out at a raised wave priority, ahead of the other
-        // wavefronts' arithmetic on the SIMD (265 against 267 us per launch on the
-        // rotating-field cascade)
-        __builtin_amdgcn_s_setprio(1);
-        nxt = load_photons(S, base + 64, end, lane);
-        __builtin_amdgcn_s_setprio(0);
-      } else {
-        has_next = wr.next(a, a.pho_pref, a.n_inst, false, tn);
-        if (has_next) nxt = load_photons(S, wave_uniform(tn.cur), wave_uniform(tn.end), lane);
-      }
-      double* X = S.x + base;
-      double* Y = S.y + base;
-      double* Z = S.z + base;
-      bool cand = false;
-      int kcand = 0;
-      const uint64_t id = in.id;
-      V3 x = in.x;
-      const V3 kv = in.k;
-      const Root kr = root_of(dot(kv, kv));
-      const double kabs = kr.r, inv_k = kr.under(1.0);
-      const bool live = id != QED_ID_DEAD;
-      const bool ok = live && kabs > 0.0 && isfinite(kabs);
-      if (live && !ok) block_count(bs, kPfNonfinite);
-      wc.adv0 += __popcll(wave_ballot(ok));
-      if (ok) {
-        if (FMODE == kFieldLocal) field_at_position<true>(fld, a.inst[inst].amp, x, E, B);
-        const PhotonSetup st = photon_setup<MIXED, FMODE != kFieldE>(a, E, B, kv, kabs, inv_k,
-                                                                     sbound, &bs);
-        int k = 0;
-        for (; k < st.nsub; ++k) {
-          if (a.push_photons) x = {x.x + st.hk * kv.x, x.y + st.hk * kv.y, x.z + st.hk * kv.z};
-          if (!a.pairs) continue;
-          if (!bound_reachable<MIXED>(st.pbound)) {
-            cnt.early += a.runs_pair;
-            continue;
-          }
-          // a candidate if the draw of any run (N_g of them in the reverse mode of Sec. VI)
-          // falls below the bound
-          bool hit = below_bound<MIXED>(draw_words(id, seed, step, (uint32_t)k, kDraw),
-                                        st.pbound);
-          for (int run = 1; run < a.runs_pair && !hit; ++run)
-            hit = below_bound<MIXED>(draw_words(id, seed, step, sub_code(k, run), kDraw),
-                                     st.pbound);
-          if (hit) {
-            cand = true;
-            kcand = k;
-            break;
-          }
+  // Software pipeline: DEPTH batches of 64 photons are requested before the current one is
+  // processed, so each wavefront keeps loads in flight while it computes.  One in a launch of
+  // its own (four wavefronts per SIMD and more), two beside the leptons, whose registers and LDS
+  // leave three wavefronts per SIMD or two.  With one batch, and look-ups in between that
+  // waited for all loads, a step of 2 10^5 leptons and 1.6 10^7 photons took 361 us in the
+  // rotating field and 423 in a uniform B (FP64), against 346 and 357 in a launch each; with
+  // two 335 and 345.
+  int inst = -1;
+  uint64_t seed = 0;
+  double amp = 0.0;
+  V3 Ei{}, Bi{};
+  auto process = [&](const PhotonIn& in, long long base, long long g0, int n) {
+    V3 E = Ei, B = Bi;
+    double* X = S.x + base;
+    double* Y = S.y + base;
+    double* Z = S.z + base;
+    bool cand = false;
+    int kcand = 0;
+    const uint64_t id = in.id;
+    V3 x = in.x;
+    const V3 kv = in.k;
+    const Root kr = root_of(dot(kv, kv));
+    const double kabs = kr.r, inv_k = kr.under(1.0);
+    const bool live = lane < n && id != QED_ID_DEAD;
+    const bool ok = live && kabs > 0.0 && isfinite(kabs);
+    if (live && !ok) block_count(bs, kPfNonfinite);
+    wc.adv0 += __popcll(wave_ballot(ok));
+    if (ok) {
+      if (FMODE == kFieldLocal) field_at_position<true>(fld, amp, x, E, B);
+      const PhotonSetup ps = photon_setup<MIXED, FMODE != kFieldE>(a, E, B, kv, kabs, inv_k,
+                                                                   sbound, &bs);
+      int k = 0;
+      for (; k < ps.nsub; ++k) {
+        if (a.push_photons) x = {x.x + ps.hk * kv.x, x.y + ps.hk * kv.y, x.z + ps.hk * kv.z};
+        if (!a.pairs) continue;
+        if (!bound_reachable<MIXED>(ps.pbound)) {
           cnt.early += a.runs_pair;
+          continue;
         }
-        if (!cand) {
-          cnt.subs += st.nsub;
-          if (a.push_photons) {
-            // streaming stores: the positions are not read again in this step (1% faster
-            // than plain stores; reading the positions non-temporally as well was slower)
-            __builtin_nontemporal_store(x.x, &X[lane]);
-            __builtin_nontemporal_store(x.y, &Y[lane]);
-            __builtin_nontemporal_store(x.z, &Z[lane]);
-          }
-        } else {
-          cnt.subs += kcand;  // the exact kernel counts the rest
+        // a candidate if the draw of any run (N_g of them in the reverse mode of Sec. VI)
+        // falls below the bound
+        bool hit = below_bound<MIXED>(draw_words(id, seed, step, (uint32_t)k, kDraw),
+                                      ps.pbound);
+        for (int run = 1; run < a.runs_pair && !hit; ++run)
+          hit = below_bound<MIXED>(draw_words(id, seed, step, sub_code(k, run), kDraw),
+                                   ps.pbound);
+        if (hit) {
+          cand = true;
+          kcand = k;
+          break;
         }
+        cnt.early += a.runs_pair;
       }
-      // ---- record candidates: (photon index << 16) | sub-step ----
-      const uint64_t cm = wave_ballot(cand);
-      if (cm) {
-        const int nc = __popcll(cm);
-        const unsigned long long e =
-            ((unsigned long long)(g0 + (base - cur) + lane) << 16) | (unsigned long long)kcand;
-        if (ncand + nc <= a.cand_per_wave) {
-          if (cand) clist[ncand + __popcll(cm & below)] = e;
-          ncand += nc;
-        } else {
-          unsigned long long pos = 0;
-          if (lane == 0) pos = atomicAdd(&hdr->n_cand, (unsigned long long)nc);
-          pos = (unsigned long long)wave_bcast((long long)pos, 0) + (unsigned long long)__popcll(cm & below);
-          // the overflow list holds one entry per photon slot: never full
-          if (cand && pos < (unsigned long long)a.cand_cap) a.cand[pos] = e;
+      if (!cand) {
+        cnt.subs += ps.nsub;
+        if (a.push_photons) {
+          // streaming stores: the positions are not read again in this step (1% faster
+          // than plain stores; reading the positions non-temporally as well was slower)
+          __builtin_nontemporal_store(x.x, &X[lane]);
+          __builtin_nontemporal_store(x.y, &Y[lane]);
+          __builtin_nontemporal_store(x.z, &Z[lane]);
         }
+      } else {
+        cnt.subs += kcand;  // the exact kernel counts the rest
       }
     }
-    tc = tn;
-    has = has_next;
+    // ---- record candidates: (photon index << 16) | sub-step ----
+    const uint64_t cm = wave_ballot(cand);
+    if (cm) {
+      const int nc = __popcll(cm);
+      const unsigned long long e =
+          ((unsigned long long)(g0 + lane) << 16) | (unsigned long long)kcand;
+      if (ncand + nc <= a.cand_per_wave) {
+        if (cand) clist[ncand + __popcll(cm & below)] = e;
+        ncand += nc;
+      } else {
+        unsigned long long pos = 0;
+        if (lane == 0) pos = atomicAdd(&hdr->n_cand, (unsigned long long)nc);
+        pos = (unsigned long long)wave_bcast((long long)pos, 0) + (unsigned long long)__popcll(cm & below);
+        // the overflow list holds one entry per photon slot: never full
+        if (cand && pos < (unsigned long long)a.cand_cap) a.cand[pos] = e;
+      }
+    }
+  };
+  auto turn = [&](PhotonBatch& b) {
+    if (b.inst != inst) {
+      inst = b.inst;
+      seed = (uint64_t)wave_uniform((long long)a.inst[inst].seed);
+      if (FMODE == kFieldLocal) {
+        amp = wave_uniform(a.inst[inst].amp);
+      } else {
+        instance_fields<FMODE>(a, inst, Ei, Bi);
+        Ei = wave_uniform(Ei);
+        Bi = wave_uniform(Bi);
+      }
+    }
+    const PhotonIn in = b.in;
+    const long long base = b.base, g0 = b.g;
+    const int n = b.n;
+    st.fetch(a, S, lane, b);
+    process(in, base, g0, n);
+  };
+  PhotonBatch b0, b1;
+  st.fetch(a, S, lane, b0);
+  if (DEPTH > 1) st.fetch(a, S, lane, b1);
+  while (b0.n > 0) {
+    turn(b0);
+    if (DEPTH > 1) {
+      if (b1.n <= 0) break;
+      turn(b1);
+    }
   }
   if (lane == 0) a.candn[wid] = (unsigned)ncand;
   wave_to_block(bs, cnt, wc);
@@ -1649,7 +1717,7 @@ __device__ __forceinline__ void photon_step(const StepArgs& a, Place at, PhotonL
 template <bool MIXED, int FMODE>
 __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
   __shared__ PhotonLds lds;
-  photon_step<MIXED, FMODE>(a, launch_place(), lds);
+  photon_step<MIXED, FMODE, 1>(a, launch_place(), lds);
 }
 
 // Leptons and photons of a step in one launch (no same-step children): neither reads what the
@@ -1694,7 +1762,7 @@ __global__ void __launch_bounds__(256)
   }
   at.grid = lep ? lep_grid : pho_grid;
   if (lep) lepton_step<MIXED, FMODE, false, false>(a, at, lds.lep);
-  else photon_step<MIXED, FMODE>(a, at, lds.pho);
+  else photon_step<MIXED, FMODE, 2>(a, at, lds.pho);
 }
 
 // State of one wavefront of the exact pair-decision kernel.
