@@ -46,9 +46,9 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 int g_cu_count[kMaxDevices];
-// [precision][field mode][kernel: photon, lepton, extended lepton, reverse-mode lepton]
+// [precision][field mode][kernel: photon, lepton, extended lepton, reverse-mode lepton, both]
 // resident 256-thread blocks per CU
-int g_occ[kMaxDevices][2][3][4];
+int g_occ[kMaxDevices][2][3][5];
 
 bool device_geometry(int* cus, int precision, int fmode, int kernel, int block, int* per_cu) {
   int dev = 0;
@@ -62,7 +62,7 @@ bool device_geometry(int* cus, int precision, int fmode, int kernel, int block, 
     g_cu_count[dev] = n;
   }
   *cus = g_cu_count[dev];
-  if (fmode < 0 || fmode > 2 || kernel < 0 || kernel > 3) return false;
+  if (fmode < 0 || fmode > 2 || kernel < 0 || kernel > 4) return false;
   if (block == 256) {
     int& o = g_occ[dev][precision == QED_MIXED ? 1 : 0][fmode][kernel];
     if (o == 0) o = step_blocks_per_cu(precision, fmode, kernel, 256);
@@ -320,7 +320,13 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   // the lepton kernel's extended form runs with same-step processing, a photon generator
   // factor or its reverse mode (the launch makes the same choice)
   const bool lep_ext = G > 0 || P.f_photon > 1.0 || P.runs_photon > 1;
-  const int lep_kernel = P.runs_photon > 1 ? 3 : lep_ext ? 2 : 1;
+  // Leptons and photons in one launch, unless the caller times them apart (events), with
+  // workgroups of 256: the shared kernel's LDS is the leptons', a table for each workgroup, and
+  // photon workgroups of 64 fit four times fewer of it than of a launch of their own (2.4 10^6
+  // photons, 3 10^5 leptons in a uniform B: 312 us a step against 216).
+  a.one_launch = run_photons && !lep_ext && block == 256 && !a.events[0] && !a.events[1] &&
+                 !a.events[2] && !a.events[3];
+  const int lep_kernel = P.runs_photon > 1 ? 3 : lep_ext ? 2 : a.one_launch ? 4 : 1;
   if (P.refill_min > 0)
     a.refill_min = P.refill_min;
   else
@@ -331,15 +337,10 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
     return QED_ERR_HIP;
   a.cus = cus;
   a.spread = 4ll * cus;
-  // beside photons (one launch, no events) two lepton workgroups per CU leave room for one of
-  // theirs; a launch of their own takes all it can hold
-  const bool apart = a.events[0] || a.events[1] || a.events[2] || a.events[3];
-  const bool one_launch = run_photons && !lep_ext && !apart;
-  if (one_launch && lep_per_cu > 2) lep_per_cu = 2;
-  // and the photons, who run beside them at the shared kernel's three or two wavefronts per
+  // The photons that run beside leptons, at the shared kernel's three or two wavefronts per
   // SIMD, share their work between four per SIMD as in a launch of their own at most: with five
-  // the largest rotating cascade takes 135.4 ms, with three 139.6, with four 130.1
-  if (one_launch && pho_per_cu > 1024 / block) pho_per_cu = 1024 / block;
+  // the largest rotating cascade takes 135.4 ms, with three 139.6, with four 130.1.
+  if (a.one_launch && pho_per_cu > 4) pho_per_cu = 4;
   LaunchShape lep{P.grid_blocks > 0 ? P.grid_blocks : cus * lep_per_cu, block};
   LaunchShape pho{P.grid_blocks > 0 ? P.grid_blocks : cus * pho_per_cu, block};
   if (lep.grid > kMaxGridBlocks) lep.grid = kMaxGridBlocks;
@@ -351,6 +352,8 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   const int pho_waves = pho.grid * (block / 64);
   a.pho_waves = run_photons ? pho_waves : 0;
   a.wpb = block / 64;
+  // where photons abound, two lepton workgroups per CU leave room for one of theirs
+  a.lep_beside = a.one_launch && P.grid_blocks == 0 && lep_per_cu > 2 ? (2 * cus < lep.grid ? 2 * cus : lep.grid) : 0;
   a.cand_per_wave = cand_list_entries(stores->slots[QED_PHOTON], pho_waves);
   if (arena > 0) {
     const bool on = G > 0;

@@ -366,6 +366,8 @@ struct StepArgs {
   int lep_grid, pho_grid, ex_grid;  // workgroups of the lepton, photon and exact-pair kernels
   int pho_waves;                    // wavefronts of the photon kernel
   int wpb;                          // wavefronts per workgroup of the lepton and photon kernels
+  int one_launch;              // leptons and photons in one launch; there, where photons abound,
+  int lep_beside;              // the lepton workgroups that work (0: all)
   qed_stats* stats;
   long long* d_step;
   hipEvent_t events[4];

@@ -222,6 +222,21 @@ inline int reduce_blocks(const StepArgs& a) {  // workgroups of 4 wavefronts
   return (n + 3) / 4;
 }
 
+// Lepton workgroups that share the leptons, where one launch takes photons too: a.lep_beside of
+// them, two per CU, where there are kBeside times as many photons, which then fill the rest of
+// each CU, else all that the device holds (the ones past the count are idle).  Only forms that
+// hold three per CU have the choice (FP64 in a rotating field, mixed in any uniform one).  us a
+// step of 10^6 leptons with two / three per CU, FP64 rotating, mixed rotating, mixed uniform:
+//   10^3 photons    114 / 99    106 / 93    131 / 114
+//   10^6            131 / 126   121 / 120   150 / 139
+//   4 10^6          172 / 169   162 / 169   191 / 189
+//   8 10^6          229 / 246   223 / 248   258 / 274
+constexpr long long kBeside = 2;
+__device__ __forceinline__ int lepton_blocks(const StepArgs& a) {
+  return a.lep_beside > 0 && a.hdr->pho_total >= kBeside * a.hdr->lep_total ? a.lep_beside
+                                                                            : a.lep_grid;
+}
+
 __device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, long long tile,
                                               long long spread);
 
@@ -233,7 +248,7 @@ __device__ __forceinline__ void reduce_job(const StepArgs& a, int job, int lane)
   const int g = job % groups, b0 = (job / groups) * kPfSlice;
   const bool pho = kind == 1 || kind == 2;
   // the workgroups that have stored a record: idle ones of the lepton and photon kernels do not
-  const int G = kind == 0   ? working_blocks(a.hdr->lep_total, a.lep_grid, a.wpb, a.tile, a.spread)
+  const int G = kind == 0   ? working_blocks(a.hdr->lep_total, lepton_blocks(a), a.wpb, a.tile, a.spread)
                 : kind == 1 ? working_blocks(a.hdr->pho_total, a.pho_grid, a.wpb, a.tile, 0)
                 : kind == 2 ? a.ex_grid
                             : a.gen_grid;
@@ -1724,13 +1739,13 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
 // other writes.  The leptons' arithmetic and the photons' memory traffic share the CUs, the tail
 // of one is filled by the other, and a launch is saved.  The workgroups go out in groups of one
 // per CU (a multiple of the XCDs, so that a workgroup's XCD stays its index modulo 8): the
-// leptons first, two per CU, beside one of photons at a time and then three.  Where the photons
-// are most of the work (kInterleave times the leptons or more) and bound by memory, one group of
-// leptons, two of photons, in turn, which keeps loads in flight beside both halves of the
-// leptons.  Against a launch each, same device: 64-electron cascade 3124 to 2860 us, mixed
-// cascade 28.0 to 26.2 ms, 64 mixed instances 14.4 to 12.7, grid cascade 35.3 to 32.3, largest
-// rotating cascade 141 to 134.  Leptons first throughout: 139; in turn throughout: 64 instances
-// 13.3, grid 33.3; three lepton workgroups per CU: largest 141 to 148.
+// leptons first (lepton_blocks), then the photons into the places they leave.  Where the photons
+// are most of the work (kInterleave times the leptons or more), one group of leptons and as many
+// of photons as there are to each (two, on a Yee grid and a standing wave one), in turn, which
+// keeps loads in flight beside both halves of the leptons.  Against a launch each, same device:
+// 64-electron cascade 3124 to 2860 us, mixed cascade 28.0 to 26.2 ms, 64 mixed instances 14.4
+// to 12.7, grid cascade 35.3 to 32.3, largest rotating cascade 141 to 128 (leptons first
+// throughout: 136; in turn throughout: 64 instances 13.3, grid 33.3).
 constexpr long long kInterleave = 8;
 template <bool MIXED, int FMODE>
 __global__ void __launch_bounds__(256)
@@ -1744,9 +1759,10 @@ __global__ void __launch_bounds__(256)
   // cycles of one group of lepton workgroups and `per` of photon ones; then the other leptons,
   // then the other photons
   const int b = (int)blockIdx.x, group = a.cus;
-  const int per = max(pho_grid / max(lep_grid, 1), 1);
+  const int lep_work = lepton_blocks(a);
+  const int per = max(pho_grid / lep_work, 1);
   const int cycles = a.hdr->pho_total >= kInterleave * a.hdr->lep_total
-                         ? min(lep_grid / group, pho_grid / (group * per))
+                         ? min(lep_work / group, pho_grid / (group * per))
                          : 0;
   Place at;
   bool lep;
@@ -1760,7 +1776,7 @@ __global__ void __launch_bounds__(256)
     lep = r < more;
     at.block = lep ? cycles * group + r : cycles * per * group + (r - more);
   }
-  at.grid = lep ? lep_grid : pho_grid;
+  at.grid = lep ? lep_work : pho_grid;
   if (lep) lepton_step<MIXED, FMODE, false, false>(a, at, lds.lep);
   else photon_step<MIXED, FMODE, 2>(a, at, lds.pho);
 }
@@ -2924,12 +2940,9 @@ __global__ void __launch_bounds__(256) gen_runs_kernel(StepArgs a, GenArgs q) {
 template <bool MIXED, int FMODE>
 static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape pho,
                               bool run_photons, hipStream_t s) {
-  // one launch for both kinds, unless the caller times them apart
   const bool ext = a.generations > 0 || a.fg_photon > 1.0;
-  bool fused = run_photons && !ext && a.runs_photon <= 1;
-  for (int i = 0; i < 4; ++i) fused = fused && !a.events[i];
   if (a.events[0]) (void)hipEventRecord(a.events[0], s);
-  if (fused)
+  if (a.one_launch)
     hipLaunchKernelGGL((particle_kernel<MIXED, FMODE>), dim3(lep.grid + pho.grid),
                        dim3(lep.block), 0, s, a, lep.grid, pho.grid);
   else if (a.runs_photon > 1)
@@ -2942,7 +2955,7 @@ static bool launch_persistent(const StepArgs& a, LaunchShape lep, LaunchShape ph
     hipLaunchKernelGGL((lepton_kernel<MIXED, FMODE, false>), dim3(lep.grid), dim3(lep.block), 0,
                        s, a);
   if (a.events[1]) (void)hipEventRecord(a.events[1], s);
-  if (run_photons && !fused) {
+  if (run_photons && !a.one_launch) {
     if (a.events[2]) (void)hipEventRecord(a.events[2], s);
     hipLaunchKernelGGL((photon_kernel<MIXED, FMODE>), dim3(pho.grid), dim3(pho.block), 0, s, a);
     if (a.events[3]) (void)hipEventRecord(a.events[3], s);
@@ -3026,13 +3039,15 @@ hipError_t launch_step(const StepArgs& a, int precision, LaunchShape lep, Launch
 }
 
 // Resident workgroups per CU of a step kernel: kind 0 the photon kernel, 1 the lepton
-// kernel, 2 its extended form, 3 its reverse-mode form.
+// kernel, 2 its extended form, 3 its reverse-mode form, 4 the kernel of both.
 template <bool MIXED, int FMODE>
 static int occupancy(int kind, int block) {
   int nb = 0;
   hipError_t e;
   if (kind == 0)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, photon_kernel<MIXED, FMODE>, block, 0);
+  else if (kind == 4)
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, particle_kernel<MIXED, FMODE>, block, 0);
   else if (kind == 3)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, lepton_runs_kernel<MIXED, FMODE>,
                                                      block, 0);
