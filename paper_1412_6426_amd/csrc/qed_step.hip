@@ -1746,6 +1746,13 @@ __global__ void __launch_bounds__(256) photon_kernel(StepArgs a) {
 // 64-electron cascade 3124 to 2860 us, mixed cascade 28.0 to 26.2 ms, 64 mixed instances 14.4
 // to 12.7, grid cascade 35.3 to 32.3, largest rotating cascade 141 to 128 (leptons first
 // throughout: 136; in turn throughout: 64 instances 13.3, grid 33.3).
+// kInterleave and the exception: where a photon's field is evaluated and not loaded (a standing
+// wave), arithmetic bounds the photons too, and leptons first is faster at every ratio (FP64,
+// first / in turn: 8 times the photons 350 / 359 us a step, 16 times 337 / 400, 80 times 413 /
+// 436).  Elsewhere the measured ratios disagree by form (8 times: grid 424 / 500, rotating 246 /
+// 252, uniform B 280 / 289, its mixed form 278 / 272; 16 times: grid 1311 / 1258, rotating 236 /
+// 239, uniform B 275 / 270; 80 times: mixed rotating 345 / 342, mixed uniform 358 / 333), and the
+// largest rotating cascade, 128 ms with 8, takes 137 with 16 and 136 with 32.
 constexpr long long kInterleave = 8;
 template <bool MIXED, int FMODE>
 __global__ void __launch_bounds__(256)
@@ -1761,7 +1768,8 @@ __global__ void __launch_bounds__(256)
   const int b = (int)blockIdx.x, group = a.cus;
   const int lep_work = lepton_blocks(a);
   const int per = max(pho_grid / lep_work, 1);
-  const int cycles = a.hdr->pho_total >= kInterleave * a.hdr->lep_total
+  const bool loads = FMODE != kFieldLocal || a.field.kind == QED_FIELD_YEE;
+  const int cycles = loads && a.hdr->pho_total >= kInterleave * a.hdr->lep_total
                          ? min(lep_work / group, pho_grid / (group * per))
                          : 0;
   Place at;
