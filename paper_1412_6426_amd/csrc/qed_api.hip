@@ -336,7 +336,6 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
       !device_geometry(&cus, P.precision, fmode, 0, block, &pho_per_cu))
     return QED_ERR_HIP;
   a.cus = cus;
-  a.spread = 4ll * cus;
   // The photons that run beside leptons, at the shared kernel's three or two wavefronts per
   // SIMD, share their work between four per SIMD as in a launch of their own at most: with five
   // the largest rotating cascade takes 135.4 ms, with three 139.6, with four 130.1.
@@ -351,9 +350,14 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   const int lep_waves = lep.grid * (block / 64);
   const int pho_waves = pho.grid * (block / 64);
   a.pho_waves = run_photons ? pho_waves : 0;
+  // few leptons go over one wavefront a SIMD, or over as many as there are: 4000 leptons on 64
+  // wavefronts took 62 us a step in chunks of 128 and 83 in the 1024 pieces that suit a full grid,
+  // which each wavefront then gathered one by one; 45 in one piece each
+  a.spread = 4 * cus < lep_waves ? 4 * cus : lep_waves;
   a.wpb = block / 64;
   // where photons abound, two lepton workgroups per CU leave room for one of theirs
-  a.lep_beside = a.one_launch && P.grid_blocks == 0 && lep_per_cu > 2 ? (2 * cus < lep.grid ? 2 * cus : lep.grid) : 0;
+  a.lep_beside = a.one_launch && P.grid_blocks == 0 && lep_per_cu > 2 && 2 * cus < lep.grid
+                     ? 2 * cus : 0;
   a.cand_per_wave = cand_list_entries(stores->slots[QED_PHOTON], pho_waves);
   if (arena > 0) {
     const bool on = G > 0;

@@ -342,7 +342,7 @@ struct StepArgs {
   int generations;  // children advanced in their birth step: generations (0: none)
   long long tile;    // particles per work chunk (0: chosen from the particle count)
   int cus;           // compute units of the device
-  long long spread;  // wavefronts that few leptons are spread over (one a SIMD)
+  long long spread;  // wavefronts that few leptons are spread over (one a SIMD at most)
   WorkHdr* hdr;
   long long* n0;
   long long* lep_pref;
