@@ -601,7 +601,7 @@ __global__ void __launch_bounds__(kSortThreads) thin_decide_kernel(SortArgs a, T
     const double fac = W / K;
     double Wa = 0.0;
     for (long long g = g0; g < g1; ++g)
-      if (t.keep[g]) Wa += S.w[sb + g] * fac;
+      if (t.keep[g]) Wa = fma(S.w[sb + g], fac, Wa);
     t.gfac[q] = fac;
     t.gwa[q] = Wa;
     t.gkept[q] = (unsigned)kept;
@@ -614,6 +614,17 @@ __device__ __forceinline__ double add_in_order(double sum, double v) {
 #pragma unroll
   for (int l = 0; l < 64; ++l)
     sum += __hiloint2double(__builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(lo, l));
+  return sum;
+}
+
+// sum + v fac over the lanes of `mask` in lane order, one rounding each (wavefront-uniform result).
+__device__ __forceinline__ double fma_in_order(double sum, double v, double fac, uint64_t mask) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  for (; mask; mask &= mask - 1) {
+    const int l = __ffsll((unsigned long long)mask) - 1;
+    sum = fma(__hiloint2double(__builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(lo, l)),
+              fac, sum);
+  }
   return sum;
 }
 
@@ -709,10 +720,8 @@ __global__ void __launch_bounds__(kSortThreads) thin_mid_kernel(SortArgs a, Thin
     const double fac = W / K;
     double Wa = 0.0;
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const double p = w[r] * fac;
-      if (r * 64 < m) Wa = add_in_order(Wa, (rows >> r) & 1u ? p : 0.0);
-    }
+    for (int r = 0; r < kRows; ++r)
+      if (r * 64 < m) Wa = fma_in_order(Wa, w[r], fac, wave_ballot((rows >> r) & 1u));
     if (lane == 0) {
       t.gw[q] = W;
       t.gfac[q] = fac;
