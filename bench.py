@@ -19,7 +19,8 @@ with HIP events around each of them inside the timed run (the other steps replay
 between them); `value` is their particle-steps over their summed time, and the config lists
 the steps.  Without --steps every step is timed.  The whole job's time and rate are in the
 config too.  The roofline is taken over every launch of the dominant kernel in the eager
-run.
+run: events give leptons and photons a launch each, while the timed steps, which have
+none inside, take both in one launch (`form` says so).
 
 Prints one JSON line: the headline and its roofline, and a short summary per further leg:
 the same job in mixed precision with its photon-spectrum L1 distance and pair yield against
@@ -336,7 +337,8 @@ def gpu_run_yee(args, precision, sort_every=None, sort_species=None, thin=None):
     2000 each, cells of lambda/32, 10^6 seeds Gaussian sigma = 0.1 lambda about the node,
     dt = T/100, 2*10^8 photon slots).  The grid is refilled with the analytic wave before
     every step (a stand-in for the field solver, timed separately); steps run eagerly with
-    HIP events around the fill, the whole step, and the lepton and photon kernels.  Every
+    HIP events around the fill and the whole step, and once more from the seeds with events
+    around the lepton and photon kernels, which then get a launch each.  Every
     `sort_every` steps (0: never) the stores `sort_species` are sorted by cell
     (qed_sort_cells) before the step; that time counts as part of the step and is also
     reported apart.  thin = (fraction, cap): after each step, every store holding more slots
@@ -366,46 +368,55 @@ def gpu_run_yee(args, precision, sort_every=None, sort_species=None, thin=None):
     hip = HipEvents()
     evs = hip.create(8 * K)
     tev = hip.create(2 * K) if thin else []
-    thin_calls = 0
     if S:
         e.sort_cells(0, field, stream=sp)  # allocates the sort workspace outside the timing
     if thin:
         for s_ in range(3):  # the thinning workspace and records, outside the timing
             e.thin_cells(s_, field, 1 << 62, stream=sp)
-    torch.cuda.synchronize()
-    e.set_step(0)
-    with torch.cuda.stream(stream):
-        for n in range(K):
-            ev = evs[8 * n:8 * n + 8]
-            hip.lib.hipEventRecord(C.c_void_p(ev[0]), C.c_void_p(sp))
-            grid.fill(w.t0 + n * w.dt, sp)
-            hip.lib.hipEventRecord(C.c_void_p(ev[1]), C.c_void_p(sp))
-            if S and n % S == 0:
-                for s_ in sort_species:
-                    e.sort_cells(s_, field, stream=sp)
-            hip.lib.hipEventRecord(C.c_void_p(ev[7]), C.c_void_p(sp))
-            for j in range(4):
-                params.events[j] = ev[2 + j]
-            e.step(field, params, stream=sp)
-            hip.lib.hipEventRecord(C.c_void_p(ev[6]), C.c_void_p(sp))
-            Q.qed_append_stats(e.stats_buf.data_ptr(), log.data_ptr(), K, cnt.data_ptr(), sp)
-            if thin:
-                hip.lib.hipEventRecord(C.c_void_p(tev[2 * n]), C.c_void_p(sp))
-                stream.synchronize()
-                counts = e.counts()[0]
-                for s_ in range(3):
-                    if counts[s_] > thin[0] * w.capacity[s_]:
-                        e.thin_cells(s_, field, thin[1], stream=sp)
-                        thin_calls += 1
-                hip.lib.hipEventRecord(C.c_void_p(tev[2 * n + 1]), C.c_void_p(sp))
-    torch.cuda.synchronize()
-    for j in range(4):
-        params.events[j] = None
+
+    def from_the_seeds(apart):
+        """The K steps; apart: with events around the two kernels.  Calls of the thinning."""
+        e.reset_instances()
+        for s_ in range(3):
+            e.load(0, s_, init[s_])
+        e.set_step(0)
+        cnt.zero_()
+        torch.cuda.synchronize()
+        calls = 0
+        with torch.cuda.stream(stream):
+            for n in range(K):
+                ev = evs[8 * n:8 * n + 8]
+                hip.lib.hipEventRecord(C.c_void_p(ev[0]), C.c_void_p(sp))
+                grid.fill(w.t0 + n * w.dt, sp)
+                hip.lib.hipEventRecord(C.c_void_p(ev[1]), C.c_void_p(sp))
+                if S and n % S == 0:
+                    for s_ in sort_species:
+                        e.sort_cells(s_, field, stream=sp)
+                hip.lib.hipEventRecord(C.c_void_p(ev[7]), C.c_void_p(sp))
+                for j in range(4):
+                    params.events[j] = ev[2 + j] if apart else None
+                e.step(field, params, stream=sp)
+                hip.lib.hipEventRecord(C.c_void_p(ev[6]), C.c_void_p(sp))
+                Q.qed_append_stats(e.stats_buf.data_ptr(), log.data_ptr(), K, cnt.data_ptr(), sp)
+                if thin:
+                    hip.lib.hipEventRecord(C.c_void_p(tev[2 * n]), C.c_void_p(sp))
+                    stream.synchronize()
+                    counts = e.counts()[0]
+                    for s_ in range(3):
+                        if counts[s_] > thin[0] * w.capacity[s_]:
+                            e.thin_cells(s_, field, thin[1], stream=sp)
+                            calls += 1
+                    hip.lib.hipEventRecord(C.c_void_p(tev[2 * n + 1]), C.c_void_p(sp))
+        torch.cuda.synchronize()
+        return calls
+
+    thin_calls = from_the_seeds(apart=False)
     thin_ms = sum(hip.elapsed_ms(tev[2 * n], tev[2 * n + 1]) for n in range(K)) if thin else 0.0
-    hip.destroy(tev)
     fill_ms = sum(hip.elapsed_ms(evs[8 * n], evs[8 * n + 1]) for n in range(K))
     step_ms = sum(hip.elapsed_ms(evs[8 * n + 1], evs[8 * n + 6]) for n in range(K))
     sort_ms = sum(hip.elapsed_ms(evs[8 * n + 1], evs[8 * n + 7]) for n in range(K))
+    from_the_seeds(apart=True)
+    hip.destroy(tev)
     lep_ms = sum(hip.elapsed_ms(evs[8 * n + 2], evs[8 * n + 3]) for n in range(K))
     pho_ms = sum(hip.elapsed_ms(evs[8 * n + 4], evs[8 * n + 5]) for n in range(K))
     hip.destroy(evs)
@@ -1086,6 +1097,7 @@ def main():
         "roofline": {
             "bound": "hbm",
             "kernel": kernel_name(dom, args.precision),
+            "form": "a launch per kind, in the eager run with events (timed steps: one launch)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

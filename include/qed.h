@@ -179,7 +179,12 @@ typedef struct {
   void *events[4];      /* optional hipEvent_t recorded on `stream` right before/after the
                            lepton kernel ([0], [1]) and the photon bound kernel ([2], [3]),
                            for timing those two kernels alone; NULL entries are skipped.
-                           Owned by the caller. */
+                           Owned by the caller.  Without events (and without same-step
+                           children, a photon generator factor or its reverse mode) one launch
+                           may take leptons and photons together; any event that is not NULL
+                           gives each a launch and a resident grid of its own.  The results
+                           are the same, the step's time is not: leave them NULL outside
+                           of measurements. */
   double f_photon;      /* tunable generator factors f_g of Sec. VI for photon emission and */
   double f_pair;        /* pair creation; a value <= 1 means off.  An event still acts on its
                            parent every time it fires (the lepton recoils, the photon decays);
