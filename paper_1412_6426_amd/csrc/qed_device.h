@@ -377,11 +377,6 @@ __device__ __forceinline__ double substep_cube(double h, double inv_lep_scale) {
   const double r = h * inv_lep_scale;
   return r * r * r;
 }
-// dt / dt_q for photons: dt_q = kappa 130 (2 pi eps_r) |k| / chi_g (Eq. (33)).
-__device__ __forceinline__ double substep_ratio_photon(double dt, double chi_g, double kabs,
-                                                       double inv_pho_scale) {
-  return dt * (chi_g / kabs) * inv_pho_scale;  // inv_pho_scale = 1/(kappa 260 pi eps_r)
-}
 
 struct NsubInfo {
   int n;

@@ -131,13 +131,13 @@ struct WorkLayout {
   size_t lep_pref;  // long long [2 n_inst + 1]: particle prefix over (instance, e-/e+)
   size_t pho_pref;  // long long [n_inst + 1]: particle prefix over instances
   size_t eb;        // double [n_inst * 6]: E, B of space-independent fields at t_n
-  size_t lep_part;  // uint64 [kPfCount][kMaxGridBlocks]
-  size_t pho_part;  // uint64 [kPfCount][kMaxGridBlocks]
-  size_t ex_part;   // uint64 [kPfCount][kMaxGridBlocks]
+  size_t lep_part;  // uint64 [kPfCount kMaxGridBlocks], in PartialField's groups
+  size_t pho_part;  // the same
+  size_t ex_part;   // the same
   size_t candn;     // uint32 [kMaxWaves]: candidates per photon wavefront
   size_t candw;     // uint64 [photon slots + kMaxWaves kCandSlack]: per-wavefront lists
   size_t cand;      // uint64 [photon slots]: overflow list, (photon index << 16) | sub-step
-  size_t gen_part;  // uint64 [kPfCount][kMaxGridBlocks]: the generation kernel's partials
+  size_t gen_part;  // the same, of the generation kernel
   // child arenas (present when arena_records > 0 and n_inst <= kArenaMaxInstances); set 1
   // only with same-step processing (generations alternate between the two sets)
   size_t ph_cols[2], ph_cnt[2], ph_nrec[2], ph_base[2], ph_chain[2];  // photons from leptons
@@ -290,9 +290,11 @@ struct SortLayout {
 
 // qed_thin_cells: the sort's workspace, then per group (at most one per live slot) its first
 // item, weight factor, weight before and after, and survivors, and the list of large groups;
-// per instance the group and survivor prefixes.  The sort's second key and index arrays hold each item's group and its
-// survivor rank within its tile, its first index array the survival flags, and the count
-// array's first and second tiles_max words the per-tile group and survivor counts.
+// per instance the group and survivor prefixes.  The sort's other key and index arrays (those
+// that do not hold the sorted keys and the order) take each item's group and its survivor rank
+// within its tile, the second half of the list of large groups the survival flags (a byte each),
+// the count array's first and second tiles_max words the per-tile group and survivor counts, and
+// the factors' array, once they are applied, the partial sums of the records.
 struct ThinCellsLayout {
   SortLayout sort;
   size_t gstart, gfac, gw, gwa, gkept, big, gpfx, kpref, total;
@@ -431,8 +433,9 @@ hipError_t launch_generator_trials(const DevTables* tables, int generator, doubl
                                    long long first, long long n, double* out, void* work,
                                    hipStream_t s);
 // Persistent-grid sizing: resident workgroups per CU for the step kernels.
-// Resident workgroups per CU of the step kernel that a launch uses: the photon kernel, or
-// the lepton kernel in its plain or extended form (EXT), for a field mode (field_mode).
+// Resident workgroups per CU of the step kernel that a launch uses: the photon kernel, the
+// lepton kernel in its plain or extended form (EXT), or the kernel of both, for a field mode
+// (field_mode).
 int step_blocks_per_cu(int precision, int fmode, int kind, int block);
 int field_mode(int kind);
 

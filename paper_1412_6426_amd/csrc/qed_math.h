@@ -4,7 +4,7 @@
 // cycles per FP64 instruction, and a sub-step is a chain with little to overlap.  The library
 // takes 17 instructions for a square root, 10 for a division, 75 for a log2 (it carries a
 // double-double), 26 for an exp and 45 for a cube root; the forms here, whose operands the
-// callers keep within the ranges that each states, take 5 to 20, x^(2/3) 45.  log2 and exp are
+// callers keep within the ranges that each states, take 3 to 20, x^(2/3) 45.  log2 and exp are
 // table-driven (P. T. P. Tang, ACM TOMS 15, 144 (1989) and 16, 378 (1990)).
 //
 // None is less exact than what it stands for.  Largest errors over 10^6 arguments each against

@@ -11,7 +11,8 @@
 //   photons  (persistent)   photons: push, chi_gamma, pair-rate bound; draws below the
 //                           bound go to the wavefront's candidate list (leptons and photons
 //                           are workgroups of one launch, except with same-step children, a
-//                           generator factor, its reverse mode, or events around them) for
+//                           generator factor, its reverse mode, events around them, or
+//                           workgroups of other sizes than 256) for
 //   exact    (persistent)   the exact pair decision; pair records go to the pair arena;
 //   scan     (2 wgs/instance) arena counts -> store offsets, instance counts raised and
 //                           clamped to the capacities;
@@ -38,7 +39,7 @@
 // the GPU on one address; the arenas avoid that.  Without arena space (or with more than
 // kArenaMaxInstances instances) children are staged per wavefront in LDS and reserved in
 // batches of up to 32 with one atomic per (batch, instance, species).  Statistics are
-// reduced per workgroup in LDS and written as partials; the finalize kernel sums them.
+// reduced per workgroup in LDS and written as partials, which the reduce jobs sum.
 #include "qed_internal.h"
 
 namespace qedk {
@@ -1786,7 +1787,9 @@ __global__ void __launch_bounds__(256)
   }
   at.grid = lep ? lep_work : pho_grid;
   if (lep) lepton_step<MIXED, FMODE, false, false>(a, at, lds.lep);
-  else photon_step<MIXED, FMODE, 2>(a, at, lds.pho);
+  // (a position-dependent field's loads come back after the batches ahead of them, and a
+  // standing wave's photons wait for none: one batch)
+  else photon_step<MIXED, FMODE, FMODE == kFieldLocal ? 1 : 2>(a, at, lds.pho);
 }
 
 // State of one wavefront of the exact pair-decision kernel.
@@ -2142,10 +2145,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 // ------------------------------------------------------------------------------------
 // arena append: scan of the per-(instance, wavefront) counts, then the copy into the stores
 // ------------------------------------------------------------------------------------
-// Two workgroups per instance, photons and pairs (4.7 us a launch; 6.7 with one taking both in
-// turn): exclusive prefix over the wavefronts of the arena's counts (in place), the store
-// count before the append into base[], and the counts raised by the totals, clamped to the
-// capacities; the copy kernel drops and counts the children that land beyond them.
 // Exclusive prefix over n words by a workgroup of 1024: thread t sums the run [t k, t k + k),
 // one scan of the thread sums, then the run's offsets in place.  Returns the total; `wsum` is
 // 16 words of LDS.
@@ -2181,6 +2180,10 @@ __device__ __forceinline__ unsigned long long block_prefix(unsigned int* row, in
   return carry;
 }
 
+// Two workgroups per instance, photons and pairs (4.7 us a launch; 6.7 with one taking both in
+// turn): exclusive prefix over the wavefronts of the arena's counts (in place), the store
+// count before the append into base[], and the counts raised by the totals, clamped to the
+// capacities; the copy kernel drops and counts the children that land beyond them.
 // With same-step processing (A.slot set) one more workgroup turns each arena's record counts
 // per producing wavefront into their prefix, and the total goes to used[1], so that the next
 // generation's wavefronts find the records they are dealt.  `in_p`, `in_q`: totals of the
