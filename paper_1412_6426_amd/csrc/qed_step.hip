@@ -767,6 +767,11 @@ __device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, lo
   return grid > 0 ? (int)((working_waves(N, (long long)grid * wpb, tile, spread) + wpb - 1) / wpb)
                   : 0;
 }
+// Wavefronts of the lepton kernel that own any lepton of this step (the first ones).
+__device__ __forceinline__ int lepton_waves(const StepArgs& a) {
+  return (int)working_waves(a.hdr->lep_total, (long long)lepton_blocks(a) * a.wpb, a.tile,
+                            a.spread);
+}
 // Does this workgroup own any work?
 __device__ __forceinline__ bool block_has_work(Place at, long long N, long long tile,
                                                long long spread) {
@@ -1029,7 +1034,12 @@ __device__ __forceinline__ void flush_pairs(const StepArgs& a, PairStage& sg, in
 // cascade.  With a B field the Boris rotation's registers make that bound cost more spills
 // than the third wavefront gains (3% slower on 10^4 electrons in a uniform B), and with a
 // grid field far more (1.9 times slower), so those kernels keep the LDS table at two
-// wavefronts per SIMD.
+// wavefronts per SIMD.  The mixed form's table is half as large, and three workgroups' LDS fits a
+// CU: its kernels for space-independent fields are held to three wavefronts as well (with a B
+// field 17 registers spill; two against three wavefronts, us a step of 10^6 leptons and 10^3
+// photons: rotating 109 / 94, uniform B 123 / 113; with 10^6 photons 138 / 120, 152 / 136; leptons
+// alone 102 / 91, 119 / 110).  The extended forms get two at least, one in a
+// position-dependent field needs 256 VGPRs and spills a few.
 template <bool MIXED, int FMODE, bool EXT>
 struct LeptonShape {
   static constexpr bool global_table = !MIXED && FMODE == kFieldE && !EXT;
@@ -2209,7 +2219,9 @@ __global__ void __launch_bounds__(1024) arena_scan_kernel(StepArgs a, ChildArena
   const int kind = (int)(blockIdx.x & 1u);  // photons, pairs
   const ChildArena& A = kind == 0 ? pa : qa;
   unsigned long long total = 0ull;
-  if (A.waves > 0) total = block_prefix(A.cnt + (size_t)i * A.waves, A.waves, wsum);
+  // (the lepton wavefronts past the working ones have counted nothing)
+  const int n = kind == 0 && A.waves > 0 && !A.slot ? lepton_waves(a) : A.waves;
+  if (n > 0) total = block_prefix(A.cnt + (size_t)i * A.waves, n, wsum);
   if (threadIdx.x != 0) return;
   // the store counts before the append, and the new ones; counts above the capacity (the copy
   // drops and counts what lands beyond it) are clamped
@@ -2285,7 +2297,11 @@ __global__ void __launch_bounds__(256) arena_copy_kernel(StepArgs a, ChildArena 
   const uint64_t below = lanes_below();
   const int lane = lane_id();
   const uint32_t step = (uint32_t)a.hdr->step;
-  const int npa = pa.waves > 0 && !(pa.slot && pa.used[1] == 0u) ? pa.waves : 0;
+  // (the lepton wavefronts past the working ones have written nothing)
+  const int npa = pa.waves <= 0    ? 0
+                  : !pa.slot       ? lepton_waves(a)
+                  : pa.used[1] > 0 ? pa.waves
+                                   : 0;
   const int nqa = qa.waves > 0 && !(qa.slot && qa.used[1] == 0u) ? qa.waves : 0;
   const int V = nblk * (int)(blockDim.x >> 6);
   const int wid = blk * (int)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
