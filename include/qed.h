@@ -170,8 +170,9 @@ typedef struct {
   int freeze_on_drop;   /* 1: an instance that dropped children is frozen from the next step */
   int tile;             /* work split: each wavefront takes chunks of `tile` consecutive
                            particles, dealt round-robin, so that at any moment the
-                           wavefronts stream through neighbouring memory; 0 = 128, and less where
-                           that would leave wavefronts without work.  A tile of
+                           wavefronts stream through neighbouring memory; 0 = from their count, up
+                           to 128 leptons and 512 photons (128 on a Yee grid), and less
+                           where that would leave wavefronts without work.  A tile of
                            at least N / wavefronts gives one contiguous chunk per wavefront */
   int block;            /* threads per workgroup (64..256, multiple of 64); 0 = 256 */
   int grid_blocks;      /* persistent workgroups per kernel (<= 4096); 0 = resident

@@ -45,8 +45,8 @@ DEFAULT_SHAPE: Shape = (0, 0, 0, 0)
 
 
 def default_candidates(cu_count: int) -> List[Shape]:
-    """The library's own chunk rule (tile 0: 128 particles, fewer where that leaves wavefronts
-    without work) and chunks of 64..512 particles on its resident grid, and the rule on
+    """The library's own chunk rule (tile 0: up to 128 leptons and 512 photons, fewer where that
+    leaves wavefronts without work) and chunks of 64..512 particles on its resident grid, and the rule on
     smaller and larger grids."""
     return [DEFAULT_SHAPE, (64, 0, 0, 0), (128, 0, 0, 0), (256, 0, 0, 0), (512, 0, 0, 0),
             (0, 2 * cu_count, 0, 0), (0, 8 * cu_count, 0, 0)]

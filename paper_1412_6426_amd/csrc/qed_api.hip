@@ -277,7 +277,6 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   a.pairs = P.pairs;
   a.push_photons = P.push_photons;
   a.freeze_on_drop = P.freeze_on_drop;
-  a.tile = P.tile;
   // the largest child arena the workspace holds (sizes are monotonic in the record count)
   long long arena = 0;
   if (ni <= kArenaMaxInstances &&
@@ -336,10 +335,10 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
       !device_geometry(&cus, P.precision, fmode, 0, block, &pho_per_cu))
     return QED_ERR_HIP;
   a.cus = cus;
-  // The photons that run beside leptons, at the shared kernel's three or two wavefronts per
-  // SIMD, share their work between four per SIMD as in a launch of their own at most: with five
-  // the largest rotating cascade takes 135.4 ms, with three 139.6, with four 130.1.
-  if (a.one_launch && pho_per_cu > 4) pho_per_cu = 4;
+  // Photons share their work between four wavefronts per SIMD at most.  Beside leptons, where
+  // three fit, the largest rotating cascade takes 130.1 ms so (139.6 with three, 135.4 with
+  // five); alone, where five fit, the same job's photon kernel 257 us a launch (262 with five).
+  if (pho_per_cu > 1024 / block) pho_per_cu = 1024 / block;
   LaunchShape lep{P.grid_blocks > 0 ? P.grid_blocks : cus * lep_per_cu, block};
   LaunchShape pho{P.grid_blocks > 0 ? P.grid_blocks : cus * pho_per_cu, block};
   if (lep.grid > kMaxGridBlocks) lep.grid = kMaxGridBlocks;
@@ -353,7 +352,8 @@ qed_status qed_step(const void* d_tables, const qed_stores* stores, const qed_fi
   // few leptons go over one wavefront a SIMD, or over as many as there are: 4000 leptons on 64
   // wavefronts took 62 us a step in chunks of 128 and 83 in the 1024 pieces that suit a full grid,
   // which each wavefront then gathered one by one; 45 in one piece each
-  a.spread = 4 * cus < lep_waves ? 4 * cus : lep_waves;
+  a.lep_deal = {P.tile, 128, 4 * cus < lep_waves ? 4 * cus : lep_waves};
+  a.pho_deal = {P.tile, field->kind == QED_FIELD_YEE ? 128 : 512, 0};
   a.wpb = block / 64;
   // where photons abound, two lepton workgroups per CU leave room for one of theirs
   a.lep_beside = a.one_launch && P.grid_blocks == 0 && lep_per_cu > 2 && 2 * cus < lep.grid

@@ -321,6 +321,13 @@ struct ThinCellsLayout {
   }
 };
 
+// How the particles of a kind are cut into work chunks.
+struct Deal {
+  long long tile;    // particles per chunk (0: chosen from their count)
+  long long most;    // the largest chunk then (128 or 512)
+  long long spread;  // wavefronts that few of them are spread over (0: batches of 64 at least)
+};
+
 struct StepArgs {
   qed_soa sp[3];
   qed_instance* inst;
@@ -342,9 +349,8 @@ struct StepArgs {
   int refill_min;  // a lepton wavefront refills idle lanes once this many are idle (or all)
   int adaptive, forced, emission, pairs, push_photons, freeze_on_drop;
   int generations;  // children advanced in their birth step: generations (0: none)
-  long long tile;    // particles per work chunk (0: chosen from the particle count)
+  Deal lep_deal, pho_deal;
   int cus;           // compute units of the device
-  long long spread;  // wavefronts that few leptons are spread over (one a SIMD at most)
   WorkHdr* hdr;
   long long* n0;
   long long* lep_pref;

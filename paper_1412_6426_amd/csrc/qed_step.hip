@@ -46,26 +46,31 @@ namespace qedk {
 
 constexpr int kWavesPerBlock = 4;  // launch bound 256 threads
 constexpr int kStageCap = 32;      // staged photon children per wavefront
-// Default work chunk: 128 particles dealt round-robin, so the wavefronts of the GPU read
-// neighbouring 512-byte pieces of every column at any moment (measured faster than one
-// contiguous range per wavefront, which scatters the reads over the whole store).
-constexpr long long kDefaultTile = 128;
-
-// Particles per chunk for N particles on W wavefronts.  Asked for: that.  Else kDefaultTile
-// while every wavefront gets a chunk; below that 64, one batch of lanes each, so that no
-// wavefront takes two batches in turn beside idle ones; and where there are fewer than 64
-// leptons for each of `spread` wavefronts (one a SIMD; 0 for the photons, whose loads want
-// full batches), as few as spread them over all of those.  A lepton's sub-steps are a serial
-// chain, and one of a wavefront with few lanes takes 1.3 us where a full one, with emissions
-// in nearly every sub-step, takes 3.7.  Against 128 throughout: 10^4 electrons in a uniform B
-// 78 to 55 us a step, the lepton kernel of 400 electrons with thousands of sub-steps each 5.7
-// to 3.5 ms.
-__device__ __forceinline__ long long chunk_size(long long N, long long W, long long tile,
-                                                long long spread) {
-  if (tile > 0) return tile;
-  if (N >= kDefaultTile * W) return kDefaultTile;
-  if (spread <= 0 || N >= 64 * spread) return 64;
-  const unsigned t = ((unsigned)N + (unsigned)spread - 1u) / (unsigned)spread;
+// Particles per chunk for N particles on W wavefronts.  Asked for (d.tile): that.  Else the
+// largest of 128, 256 and 512 up to d.most that gives every wavefront a chunk; below that 64,
+// one batch of lanes each, so that no wavefront takes two batches in turn beside idle ones; and
+// where there are fewer than 64 leptons for each of d.spread wavefronts (one a SIMD; 0 for the
+// photons, whose loads want full batches), as few as spread them over all of those.
+//
+// Chunks are dealt round-robin, so the wavefronts of the GPU read neighbouring pieces of every
+// column at any moment (measured faster than one contiguous range per wavefront, which scatters
+// the reads over the whole store).  d.most: 128 leptons, whose sub-steps differ (512: 75 against
+// 63 ms of lepton kernel on the rotating cascade); 512 photons, in whose chunks several
+// batches follow each other in memory (128 / 256 / 512 / 1024: the same job 239 / 225 / 224 / 226
+// ms, its photon kernel alone 263 / 256 / 251 / 258 us a launch); 128 photons on a Yee grid,
+// where neighbouring wavefronts share the grid's lines (8 times the photons of 10^6 leptons: 1214 /
+// 1221 / 1247 / 1256 us a step).
+//
+// A lepton's sub-steps are a serial chain, and one of a wavefront with few lanes takes 1.3 us
+// where a full one, with emissions in nearly every sub-step, takes 3.7.  Against 128 throughout:
+// 10^4 electrons in a uniform B 78 to 55 us a step, the lepton kernel of 400 electrons with
+// thousands of sub-steps each 5.7 to 3.5 ms.
+__device__ __forceinline__ long long chunk_size(long long N, long long W, const Deal& d) {
+  if (d.tile > 0) return d.tile;
+  if (N >= 128 * W) return d.most == 128 || N < 256 * W ? 128 : N < 512 * W ? 256 : 512;
+  if (d.spread <= 0 || N >= 64 * d.spread) return 64;
+  const unsigned spread = (unsigned)d.spread;
+  const unsigned t = ((unsigned)N + spread - 1u) / spread;
   return t < 1u ? 1 : (long long)t;
 }
 
@@ -238,8 +243,7 @@ __device__ __forceinline__ int lepton_blocks(const StepArgs& a) {
                                                                             : a.lep_grid;
 }
 
-__device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, long long tile,
-                                              long long spread);
+__device__ __forceinline__ int working_blocks_of(long long N, int grid, int wpb, const Deal& d);
 
 __device__ __forceinline__ void reduce_job(const StepArgs& a, int job, int lane) {
   int kind = 0;
@@ -249,8 +253,8 @@ __device__ __forceinline__ void reduce_job(const StepArgs& a, int job, int lane)
   const int g = job % groups, b0 = (job / groups) * kPfSlice;
   const bool pho = kind == 1 || kind == 2;
   // the workgroups that have stored a record: idle ones of the lepton and photon kernels do not
-  const int G = kind == 0   ? working_blocks(a.hdr->lep_total, lepton_blocks(a), a.wpb, a.tile, a.spread)
-                : kind == 1 ? working_blocks(a.hdr->pho_total, a.pho_grid, a.wpb, a.tile, 0)
+  const int G = kind == 0   ? working_blocks_of(a.hdr->lep_total, lepton_blocks(a), a.wpb, a.lep_deal)
+                : kind == 1 ? working_blocks_of(a.hdr->pho_total, a.pho_grid, a.wpb, a.pho_deal)
                 : kind == 2 ? a.ex_grid
                             : a.gen_grid;
   if (b0 >= G) return;
@@ -708,11 +712,11 @@ struct TileCursor {
 struct WaveRange {
   long long g, gend, chunk, T, W, N;
 
-  __device__ __forceinline__ void init(Place at, long long n, long long tile, long long spread) {
+  __device__ __forceinline__ void init(Place at, long long n, long long t) {
     W = (long long)at.grid * (blockDim.x >> 6);
     const long long wv = wave_index(at);
     N = n;
-    T = chunk_size(N, W, tile, spread);
+    T = t;
     chunk = wv - W;
     g = gend = 0;
   }
@@ -751,31 +755,28 @@ struct WaveRange {
   }
 };
 
-// Wavefronts of a kernel of W that own any of N particles (the first ones), and workgroups.
-__device__ __forceinline__ long long working_waves(long long N, long long W, long long tile,
-                                                   long long spread) {
-  const long long T = chunk_size(N, W, tile, spread);
+// Wavefronts of a kernel of W that own any of N particles in chunks of T (the first ones), and
+// workgroups.
+__device__ __forceinline__ long long working_waves(long long N, long long W, long long T) {
   // (a 64-bit division costs every workgroup of a launch 0.1 us)
-  const long long n = T == kDefaultTile        ? (N + (kDefaultTile - 1)) / kDefaultTile
-                      : T == 64                ? (N + 63) / 64
+  const int s = T == 128 ? 7 : T == 64 ? 6 : T == 256 ? 8 : T == 512 ? 9 : 0;
+  const long long n = s                        ? (N + T - 1) >> s
                       : N < (1ll << 31) - T    ? (long long)(((unsigned)N + (unsigned)T - 1u) / (unsigned)T)
                                                : (N + T - 1) / T;
   return n < W ? n : W;
 }
-__device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, long long tile,
-                                              long long spread) {
-  return grid > 0 ? (int)((working_waves(N, (long long)grid * wpb, tile, spread) + wpb - 1) / wpb)
-                  : 0;
+__device__ __forceinline__ int working_blocks(long long N, int grid, int wpb, long long T) {
+  return grid > 0 ? (int)((working_waves(N, (long long)grid * wpb, T) + wpb - 1) / wpb) : 0;
 }
-// Wavefronts of the lepton kernel that own any lepton of this step (the first ones).
-__device__ __forceinline__ int lepton_waves(const StepArgs& a) {
-  return (int)working_waves(a.hdr->lep_total, (long long)lepton_blocks(a) * a.wpb, a.tile,
-                            a.spread);
+__device__ __forceinline__ int working_blocks_of(long long N, int grid, int wpb, const Deal& d) {
+  return working_blocks(N, grid, wpb, chunk_size(N, (long long)grid * wpb, d));
 }
-// Does this workgroup own any work?
-__device__ __forceinline__ bool block_has_work(Place at, long long N, long long tile,
-                                               long long spread) {
-  return at.block < working_blocks(N, at.grid, (int)(blockDim.x >> 6), tile, spread);
+// The chunk of a kind's workgroups, and does this one own any work?
+__device__ __forceinline__ long long block_chunk(Place at, long long N, const Deal& d) {
+  return chunk_size(N, (long long)at.grid * (blockDim.x >> 6), d);
+}
+__device__ __forceinline__ bool block_has_work(Place at, long long N, long long T) {
+  return at.block < working_blocks(N, at.grid, (int)(blockDim.x >> 6), T);
 }
 
 template <bool MIXED>
@@ -1068,7 +1069,8 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a, Place at,
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->lep_total;
   const int wid = wave_index(at);
-  if (!block_has_work(at, N, a.tile, a.spread)) {
+  const long long chunk = block_chunk(at, N, a.lep_deal);
+  if (!block_has_work(at, N, chunk)) {
     if (a.pa.waves > 0 && lane_id() == 0) a.pa.nrec[wid] = 0u;
     return;
   }
@@ -1097,7 +1099,7 @@ __device__ __forceinline__ void lepton_step(const StepArgs& a, Place at,
   WaveCounters wc;
   TileCursor tc;
   WaveRange wr;
-  wr.init(at, N, a.tile, a.spread);
+  wr.init(at, N, chunk);
   bool open = true;
   int staged = 0;
   // arena: this wavefront's share, then pool chunks
@@ -1602,7 +1604,8 @@ __device__ __forceinline__ void photon_step(const StepArgs& a, Place at, PhotonL
   WorkHdr* hdr = a.hdr;
   const long long N = hdr->pho_total;
   const int wid = wave_index(at);
-  if (!block_has_work(at, N, a.tile, 0)) return;
+  const long long chunk = block_chunk(at, N, a.pho_deal);
+  if (!block_has_work(at, N, chunk)) return;
   block_stats_init(bs);
   stage_bounds<MIXED>(a, sbound);
   __syncthreads();
@@ -1620,7 +1623,7 @@ __device__ __forceinline__ void photon_step(const StepArgs& a, Place at, PhotonL
   cnt.bs = &bs;
   WaveCounters wc;
   PhotonStream st;
-  st.wr.init(at, N, a.tile, 0);
+  st.wr.init(at, N, chunk);
 
   // Software pipeline: DEPTH batches of 64 photons are requested before the current one is
   // processed, so each wavefront keeps loads in flight while it computes.  One in a launch of
@@ -1775,7 +1778,7 @@ __global__ void __launch_bounds__(256)
     __device__ Lds() {}
   } lds;
   // cycles of one group of lepton workgroups and `per` of photon ones; then the other leptons,
-  // then the other photons
+  // then the other photons, and last the lepton workgroups without work
   const int b = (int)blockIdx.x, group = a.cus;
   const int lep_work = lepton_blocks(a);
   const int per = max(pho_grid / lep_work, 1);
@@ -1791,15 +1794,19 @@ __global__ void __launch_bounds__(256)
     lep = w == 0;
     at.block = (lep ? c : c * per + w - 1) * group + (b - g * group);
   } else {
-    const int more = lep_grid - cycles * group;
-    lep = r < more;
-    at.block = lep ? cycles * group + r : cycles * per * group + (r - more);
+    const int more = lep_work - cycles * group, pho = pho_grid - cycles * per * group;
+    lep = r < more || r >= more + pho;
+    at.block = r < more ? cycles * group + r
+               : lep    ? lep_work + (r - more - pho)
+                        : cycles * per * group + (r - more);
   }
   at.grid = lep ? lep_work : pho_grid;
   if (lep) lepton_step<MIXED, FMODE, false, false>(a, at, lds.lep);
-  // (a position-dependent field's loads come back after the batches ahead of them, and a
-  // standing wave's photons wait for none: one batch)
-  else photon_step<MIXED, FMODE, FMODE == kFieldLocal ? 1 : 2>(a, at, lds.pho);
+  // (one batch where a second bought nothing: a position-dependent field, whose loads come back
+  // after the batches ahead of them, and the mixed rotating form: its cascade 26.03 ms, 26.24
+  // with two, though 80 photons a lepton take 323 us with two and 335 with one)
+  else photon_step<MIXED, FMODE,
+                   FMODE == kFieldLocal || (MIXED && FMODE == kFieldE) ? 1 : 2>(a, at, lds.pho);
 }
 
 // State of one wavefront of the exact pair-decision kernel.
@@ -2058,7 +2065,8 @@ __device__ __forceinline__ void exact_pass(const StepArgs& a) {
   // candidates are one index space, 64 at a time per wavefront: the lists hold a few each, and
   // a wavefront that took list after list waited for the columns of each in turn (mixed
   // cascade, 14.2 to 11.4 us a launch; 9.4 to 3 where there is no candidate).
-  const int lists = (int)working_waves(hdr->pho_total, a.pho_waves, a.tile, 0);
+  const long long chunk = chunk_size(hdr->pho_total, a.pho_waves, a.pho_deal);
+  const int lists = (int)working_waves(hdr->pho_total, a.pho_waves, chunk);
   const int per = (lists + (int)gridDim.x - 1) / (int)gridDim.x;  // <= kExactLists
   const int l0 = (int)blockIdx.x * per < lists ? (int)blockIdx.x * per : lists;
   const int nl = l0 + per < lists ? per : lists - l0;
@@ -2219,9 +2227,7 @@ __global__ void __launch_bounds__(1024) arena_scan_kernel(StepArgs a, ChildArena
   const int kind = (int)(blockIdx.x & 1u);  // photons, pairs
   const ChildArena& A = kind == 0 ? pa : qa;
   unsigned long long total = 0ull;
-  // (the lepton wavefronts past the working ones have counted nothing)
-  const int n = kind == 0 && A.waves > 0 && !A.slot ? lepton_waves(a) : A.waves;
-  if (n > 0) total = block_prefix(A.cnt + (size_t)i * A.waves, n, wsum);
+  if (A.waves > 0) total = block_prefix(A.cnt + (size_t)i * A.waves, A.waves, wsum);
   if (threadIdx.x != 0) return;
   // the store counts before the append, and the new ones; counts above the capacity (the copy
   // drops and counts what lands beyond it) are clamped
@@ -2297,11 +2303,7 @@ __global__ void __launch_bounds__(256) arena_copy_kernel(StepArgs a, ChildArena 
   const uint64_t below = lanes_below();
   const int lane = lane_id();
   const uint32_t step = (uint32_t)a.hdr->step;
-  // (the lepton wavefronts past the working ones have written nothing)
-  const int npa = pa.waves <= 0    ? 0
-                  : !pa.slot       ? lepton_waves(a)
-                  : pa.used[1] > 0 ? pa.waves
-                                   : 0;
+  const int npa = pa.waves > 0 && !(pa.slot && pa.used[1] == 0u) ? pa.waves : 0;
   const int nqa = qa.waves > 0 && !(qa.slot && qa.used[1] == 0u) ? qa.waves : 0;
   const int V = nblk * (int)(blockDim.x >> 6);
   const int wid = blk * (int)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
