@@ -33,6 +33,7 @@ KERNEL_SRC = os.path.join(os.path.dirname(HERE), "csrc", "qed_step.hip")
 # The headers every kernel source includes (device helpers, launch declarations, the C ABI).
 KERNEL_HEADERS = (os.path.join(os.path.dirname(HERE), "csrc", "qed_internal.h"),
                   os.path.join(os.path.dirname(HERE), "csrc", "qed_device.h"),
+                  os.path.join(os.path.dirname(HERE), "csrc", "qed_math.h"),
                   os.path.join(os.path.dirname(os.path.dirname(HERE)), "include", "qed.h"))
 
 
